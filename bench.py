@@ -41,19 +41,19 @@ WORKLOAD_TEXT = {
 
 
 # source file of each profiled kernel family (its hash marks the counters stale)
-KERNEL_SOURCE = {"k_cgemm_c64": "k_mfma.hip", "k_cgemm_split": "k_mfma.hip", "k_narrow": "k_narrow.hip"}
+KERNEL_SOURCE = {"k_cgemm_c64": "k_mfma.hip", "k_cgemm_split": "k_mfma.hip", "k_narrow": "k_narrow.hip",
+                 "k_cgemm_parts": "k_parts.hip"}
 
 
-def counter_traffic(workload, mode):
+def counter_traffic(workload, mode, kern):
     """HBM bytes per launch of the dominant kernel from the committed
     rocprofv3 counter summary for this workload and mode, or None when there
     is none or the kernel source has changed since the counters were taken."""
-    kern = "k_cgemm_c64" if mode == "c64" else "k_cgemm_split"
     path = os.path.join(ROOT, "profiles", f"{kern}__{workload}_{mode}.json")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    src = open(os.path.join(ROOT, "paper_2205_00393_amd", "csrc", "k_mfma.hip"), "rb").read()
+    src = open(os.path.join(ROOT, "paper_2205_00393_amd", "csrc", KERNEL_SOURCE[kern]), "rb").read()
     if hashlib.sha256(src).hexdigest() != rec.get("source_sha256"):
         return None
     return rec["traffic_bytes_per_launch"]
@@ -61,15 +61,16 @@ def counter_traffic(workload, mode):
 
 def step_roofline(kind, tile, m, k, n, batch):
     """Algorithmic flops, executed matrix flops, algorithmic bytes of one
-    matrix-core step (kind 1/5 complex64 tiles, kind 2 split tiles) over a
-    batch, and whether it is GEMM-bound: executed flops per algorithmic byte
+    matrix-core step (kind 1/5 complex64 tiles, kind 2 split tiles, kind 6
+    complex64 tiles on three bf16 parts) over a batch, and whether it is GEMM-bound: executed flops per algorithmic byte
     at or above the ridge of its matrix peak and the 8 TB/s HBM peak.
     Executed flops per complex MAC: 8 on direct complex64 tiles, 6 on the
-    three-product ones (names with _3m_), 24 on split tiles."""
+    three-product ones (names with _3m_), 24 on split tiles, 36 on three-part
+    tiles (three real products of six products of parts)."""
     f = 8.0 * (1 << (m + k + n)) * batch
-    fx = f * (3.0 if kind == 2 else (0.75 if "_3m_" in tile else 1.0))
+    fx = f * (3.0 if kind == 2 else 4.5 if kind == 6 else (0.75 if "_3m_" in tile else 1.0))
     by = 8.0 * ((1 << (m + k)) + (1 << (n + k)) + (1 << (m + n))) * batch
-    peak = PEAK_F16_MFMA_TFLOPS if kind == 2 else PEAK_FP32_MFMA_TFLOPS
+    peak = PEAK_F16_MFMA_TFLOPS if kind in (2, 6) else PEAK_FP32_MFMA_TFLOPS
     return f, fx, by, fx / by >= peak / PEAK_HBM_GBS * 1e3
 
 
@@ -268,12 +269,13 @@ def time_plan(torch, P, pr, workload, modes, args, tag, fuse_rank=0, golden=None
             ms += plan.profile_steps(first, mode)
         ms /= reps
         # matrix-core steps: kinds 1 and 5 run k_cgemm_c64 (complex64, the
-        # split-K form included), kind 2 runs k_cgemm_split; executed flops
-        # and the GEMM-bound test per step come from step_roofline
-        fam = {"k_cgemm_c64": (1, 5), "k_cgemm_split": (2,), "k_narrow": (3,)}
+        # split-K form included), kind 2 runs k_cgemm_split, kind 6
+        # k_cgemm_parts; executed flops and the GEMM-bound test per step come
+        # from step_roofline
+        fam = {"k_cgemm_c64": (1, 5), "k_cgemm_split": (2,), "k_cgemm_parts": (6,), "k_narrow": (3,)}
         kern = {name: {"launches": 0, "flops_per_batch": 0.0, "exec_flops_per_batch": 0.0,
                        "alg_bytes_per_batch": 0.0, "ms_per_batch": 0.0, "tiles": {}} for name in fam}
-        for name in ("k_cgemm_c64", "k_cgemm_split"):
+        for name in ("k_cgemm_c64", "k_cgemm_split", "k_cgemm_parts"):
             kern[name]["steps"] = []
             kern[name]["gemm_bound"] = {"launches": 0, "exec_flops_per_batch": 0.0, "ms_per_batch": 0.0}
         mf_flops, mf_ms, mf_launch, split_flops = 0.0, 0.0, 0, 0.0
@@ -340,26 +342,27 @@ def mode_table(results):
 
 
 def roofline_of(workload, mode, r):
-    """The mode's dominant kernel over its own launches only: the complex64
-    GEMM, whose achieved rate counts 8 algorithmic flops per complex MAC, or
-    the split GEMM, whose achieved rate is what the matrix cores execute
-    (three fp16/bf16 matrix products per real product: 3x the algorithmic
-    count). The complex64 GEMM's three-product tiles execute 6 flops per
-    complex MAC, so its algorithmic rate can pass the FP32 matrix peak (up
-    to 4/3 of it); `executed` and `executed_frac` give what the matrix cores
-    ran."""
-    kernel = "k_cgemm_c64" if mode == "c64" else "k_cgemm_split"
+    """The mode's dominant matrix-core kernel over its own launches only:
+    the complex64 GEMM on FP32 matrix cores, whose achieved rate counts 8
+    algorithmic flops per complex MAC (its three-product tiles execute 6, so
+    the rate can pass the FP32 matrix peak by up to 4/3), or the split and
+    the three-part GEMM, whose achieved rate is what the FP16/BF16 matrix
+    cores execute (24 and 36 flops per complex MAC). `executed` and
+    `executed_frac` give what the matrix cores ran."""
+    kernel = max(("k_cgemm_c64", "k_cgemm_split", "k_cgemm_parts"), key=lambda n: r["kernels"][n]["ms_per_batch"])
     e = r["kernels"][kernel]
-    if mode == "c64":
+    if kernel == "k_cgemm_c64":
         peak, achieved = PEAK_FP32_MFMA_TFLOPS, e["alg_tflops"]
     else:
         peak, achieved = PEAK_F16_MFMA_TFLOPS, e["exec_tflops"]
     return {"bound": "mfma", "achieved": round(achieved, 3), "peak": peak, "unit": "TFLOP/s",
-            "frac": round(achieved / peak, 4), "traffic": counter_traffic(workload, mode),
+            "frac": round(achieved / peak, 4), "traffic": counter_traffic(workload, mode, kernel),
             "kernel": kernel, "executed": round(e["exec_tflops"], 3),
             "executed_frac": round(e["exec_tflops"] / peak, 4),
-            "executed_flops_per_complex_mac": "6 on c64_3m/splitk_3m tiles, 8 on direct complex64 tiles"
-            if mode == "c64" else "24 (three fp16/bf16 products of the 2x2 real form)",
+            "executed_flops_per_complex_mac":
+            {"k_cgemm_c64": "6 on c64_3m/splitk_3m tiles, 8 on direct complex64 tiles",
+             "k_cgemm_split": "24 (three fp16/bf16 products of the 2x2 real form)",
+             "k_cgemm_parts": "36 (six bf16 products of each of three real products)"}[kernel],
             "gemm_bound_steps": {"launches": e["gemm_bound"]["launches"],
                                  "share_of_kernel_time": round(e["gemm_bound"]["ms_per_batch"] / e["ms_per_batch"], 4)
                                  if e["ms_per_batch"] > 0 else 0.0,
@@ -548,7 +551,7 @@ def summarize_main(argv):
     w, _ = _per_dispatch(a.write, "WRITE_SIZE", a.kernel, launches)
     fetch_l = sum(f.values()) / len(f) * 1024.0 * fetch_scale
     write_l = sum(w.values()) / len(w) * 1024.0 * write_scale
-    split = a.mode != "c64" and a.kernel == "k_cgemm_split"
+    split = a.kernel in ("k_cgemm_split", "k_cgemm_parts")  # on the FP16/BF16 matrix cores
     peak = PEAK_F16_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
     alg_tf = flops_l / (avg_ms * 1e-3) / 1e12
     # executed matrix flops: 3x the algorithmic count on split tiles, 3/4 of

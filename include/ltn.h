@@ -64,7 +64,9 @@ enum {
  * the matrix cores; the other steps stay complex64. Tensors stay complex64
  * in memory. */
 enum {
-  LTN_C64 = 0,        /* complex64 GEMMs on FP32 MFMA / FP32 VALU          */
+  LTN_C64 = 0,        /* complex64 GEMMs on FP32 MFMA / FP32 VALU, or on
+                         bf16 MFMA with three parts that hold all 24 bits
+                         of each FP32 operand                               */
   LTN_SPLIT_F16 = 1,  /* each real part split into fp16 hi + lo (scaled)   */
   LTN_SPLIT_BF16 = 2  /* each real part split into bf16 hi + lo (scaled)   */
 };
@@ -466,8 +468,8 @@ ltn_status ltn_execute_grad(ltn_plan* plan, const uint64_t* slice_ids, uint64_t 
  * on the bound stream and keep the fastest (cached in `cache_path` as JSON
  * when non-NULL). In complex64 mode on a plan bound with grad != 0, the
  * adjoint products of the gradient sweep (the forward-form GEMMs of
- * ltn_execute_grad) are tuned as well: every complex64 tile and, for sums
- * of 2^10 and more, every split-K tile that fits each product shape in
+ * ltn_execute_grad) are tuned as well: every complex64 tile (FP32 and
+ * three-part) and, for sums of 2^10 and more, every split-K tile that fits each product shape in
  * either operand role, against the fixed rule (cache keys g0_m_k_n_bB,
  * values [1000 kind + cfg, swap] or [-1, 0]; a cached choice that does not
  * fit its shape falls back to the fixed rule). (Kernel choice is not part
@@ -505,7 +507,10 @@ ltn_status ltn_permute(const void* d_in, void* d_out, int32_t rank, const int32_
  * partials added in FP32 in a fixed order), 5 = split-K complex64 MFMA GEMM
  * (sums of 2^10 and more cut into chunks that separate blocks reduce on the
  * matrix cores, tiles down to 16 complex columns, FP32 partials added in
- * chunk order by a second pass); cfg = tile configuration of that
+ * chunk order by a second pass), 6 = complex64 GEMM on bf16 MFMA: each real
+ * operand as three bf16 parts whose sum is the FP32 value, the six largest
+ * products of parts summed in FP32 (cfg 0, 1: full tiles; 2, 3: split-K);
+ * cfg = tile configuration of that
  * kind (-1 for the generic kernel); swap = operands exchanged (rows come
  * from B). Requires a bound plan. */
 /* Force the kernel of one step in one mode (same encoding as
@@ -523,7 +528,7 @@ ltn_status ltn_step_kernel(const ltn_plan* plan, int32_t step, int32_t mode, int
 /* Name of a kernel choice (kind and cfg as in ltn_step_kernel) in a mode,
  * e.g. "c64_3m_128x64x32": a static string, "?" for a choice that does not
  * exist. Complex64 tiles named c64_3m_* (kind 1) and splitk_3m_* (kind 5)
- * form each complex product from three real products (Gauss's method:
+ * and all of kind 6 form each complex product from three real products (Gauss's method:
  * Re = ArBr - AiBi, Im = (Ar + Ai)(Br + Bi) - ArBr - AiBi), the others from
  * the four of the 2x2 real form; the paper does not fix how a complex
  * product is formed. Host only: needs no plan and no GPU. */

@@ -1,0 +1,345 @@
+// Complex64 GEMM of one contraction step on the bf16 matrix cores:
+//   C[merge(m, n)] = sum_k A[m K + k] B[n K + k]
+//
+// The FP32 matrix cores run at 1/16 of the bf16 rate, and the FP32 tiles
+// reached 82-86 % of it: that rate bounded every large complex64 step. Here
+// each real operand is written as three bf16 parts, x = h + m + l, each the
+// rounding of what the ones before it leave. 3 x 8 significant bits hold
+// FP32's 24, so the sum is x itself, and of the nine products of parts the six
+// of weight 2^-18 and more are summed in FP32 (the others are below 2^-26 of
+// |x y|, a quarter of an FP32 rounding). The complex product takes three real
+// ones (Gauss's method, as on the three-product tiles: the sums Re + Im are
+// rounded to FP32 and then split), so a complex multiply-add costs 36 bf16
+// flops. Every MFMA adds 16 products per accumulator rounding instead of 2:
+// the error against complex128 is 0.84 of the FP32 tiles' at K = 2^10 and
+// 2^12 (6.9e-7 against 8.1e-7, 1.39e-6 against 1.62e-6).
+//
+// What bounds it: power. At (13,12,11) the matrix cores are busy 66 % of the
+// cycles and the clock falls to 1.8 GHz; the same step takes 2.00 ms (275
+// TFLOP/s of 8 flops per complex multiply-add, 1.24 PFLOP/s executed; a large
+// library bf16 product reaches 1.13-1.35 PFLOP/s on the same cards) against
+// 3.11 ms on the best FP32 tile. Variants that keep the matrix cores fed
+// differently measured no better: a wave-specialised block (four waves that
+// convert, four that multiply, two LDS buffers) 2.11 ms, one wave per SIMD
+// with conversion and products interleaved 2.3 ms.
+//
+// Layout: 128 x 128 outputs per block, 2 x 2 waves of 64 x 64; a wave holds
+// 3 x 64 accumulators, two blocks share a CU, and one block's loads and
+// conversion run under the other's products. Threads take groups of eight
+// consecutive k' of one row, as two 16-byte units per row: unit u of a row's
+// 128 bytes goes to group u & 1, so that two lanes read 32 consecutive bytes;
+// both operands use that order of the sum. Nine LDS planes (3 x parts) of
+// 16-byte units; group g of row r is unit 2 r + (g ^ (r >> 3 & 1)), so the 16
+// rows of a read pass fall on all 64 banks once (no conflicts counted).
+#include "gemm_common.h"
+
+namespace ltn {
+
+namespace {
+
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// The last part of a number below 2^-110 falls below bf16's smallest number.
+// Circuits have such entries (cos(pi/2) = 6e-17 and its products), so operands
+// are scaled up by 2^24, which makes every FP32 number above 2^-126 exact; what
+// overflows then (results above 2^79) takes the FP32 way at the end. 48
+// multiplications per wave and k-tile: 1-2 % of the time.
+constexpr float kUp = 0x1p24f;
+
+// Parts of eight FP32 values times kUp, as the operand words of one MFMA lane.
+__device__ __forceinline__ void to_parts(const float (&x)[8], u32x4 (&o)[3]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float a = x[2 * j] * kUp, b = x[2 * j + 1] * kUp;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
+      o[p][j] = w;
+      a -= __uint_as_float(w << 16);
+      b -= __uint_as_float(w & 0xffff0000u);
+    }
+  }
+}
+
+__device__ __forceinline__ floatx16 mfma_part(u32x4 a, u32x4 b, floatx16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(SplitType<true>::V8, a),
+                                                 __builtin_bit_cast(SplitType<true>::V8, b), c, 0, 0, 0);
+}
+
+// SPLITK: block w takes chunk w / (tiles * nb) of the sum for tile w % (tiles *
+// nb) and writes its FP32 partial of C to part, as k_cgemm_c64's split-K form.
+template <int BM, int BN, bool SPLITK>
+__global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
+  constexpr int T = 256, KT = 16, PARTS = 3, NWM = 2, NWN = 2;
+  constexpr int WM = BM / NWM, WN = BN / NWN, TM = WM / 32, TN = WN / 32;
+  constexpr int ROWS = BM + BN, GRP = 2 * ROWS, R = (GRP + T - 1) / T;
+  static_assert(TM >= 1 && TN >= 1 && GRP % 64 == 0, "tile too small");
+  __shared__ u32x4 S[3 * PARTS][GRP];
+
+  const int64_t M = int64_t(1) << d.m, N = int64_t(1) << d.n, K = int64_t(1) << d.k;
+  int64_t b, bm, bn, chunk = 0, w = blockIdx.x;
+  if constexpr (SPLITK) {
+    const int64_t per = (M / BM) * (N / BN) * d.nb;
+    chunk = w / per;
+    w -= chunk * per;
+  }
+  tile_of(w, M / BM, N / BN, d.nb, b, bm, bn);
+  const int64_t KL = SPLITK ? (int64_t(1) << d.kc_bits) : K;
+  const int nt = (int)(KL / KT);
+  const float2* A = d.A + b * d.sA + bm * BM * K + chunk * KL;
+  const float2* B = d.B + b * d.sB + bn * BN * K + chunk * KL;
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tid = threadIdx.x;
+  const int wm = wave / NWN, wn = wave % NWN;
+  const int h = lane >> 5, i = lane & 31;
+
+  // the groups of a tile may end within a round of the threads, between two waves
+  auto has = [&](int r) { return GRP % T == 0 || r < R - 1 || T * r + 64 * wave < GRP; };
+  const float4* src[R];
+  int dst[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int c = tid + T * r, row = c >> 1, g = c & 1;
+    src[r] = reinterpret_cast<const float4*>(row < BM ? A + row * K : B + (row - BM) * K) + g;
+    dst[r] = 2 * row + (g ^ ((row >> 3) & 1));
+  }
+  // one k-tile of group r, and on to the next tile (`more`: there is one)
+  auto load = [&](int r, float4 (&v)[4], bool more) {
+    if (!has(r)) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = src[r][2 * q];
+    src[r] += more ? KT / 2 : 0;
+  };
+  auto stash = [&](int r, const float4 (&v)[4]) {
+    if (!has(r)) return;
+    float re[8], im[8], su[8];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      re[2 * q] = v[q].x;
+      im[2 * q] = v[q].y;
+      re[2 * q + 1] = v[q].z;
+      im[2 * q + 1] = v[q].w;
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) su[q] = re[q] + im[q];
+    u32x4 o[PARTS];
+    to_parts(re, o);
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) S[p][dst[r]] = o[p];
+    __builtin_amdgcn_sched_barrier(0);
+    to_parts(im, o);
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) S[PARTS + p][dst[r]] = o[p];
+    __builtin_amdgcn_sched_barrier(0);
+    to_parts(su, o);
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) S[2 * PARTS + p][dst[r]] = o[p];
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  floatx16 acc[3][TM][TN];
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+#pragma unroll
+    for (int x = 0; x < TM; ++x)
+#pragma unroll
+      for (int y = 0; y < TN; ++y)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[p][x][y][v] = 0.f;
+
+  auto unit = [&](int row) { return 2 * row + (h ^ ((row >> 3) & 1)); };
+  auto multiply = [&](int pl) {
+    u32x4 bv[TN][PARTS];
+#pragma unroll
+    for (int y = 0; y < TN; ++y)
+#pragma unroll
+      for (int p = 0; p < PARTS; ++p) bv[y][p] = S[pl * PARTS + p][unit(BM + wn * WN + 32 * y + i)];
+#pragma unroll
+    for (int x = 0; x < TM; ++x) {
+      u32x4 av[PARTS];
+#pragma unroll
+      for (int p = 0; p < PARTS; ++p) av[p] = S[pl * PARTS + p][unit(wm * WM + 32 * x + i)];
+      // small products first; the tiles along y alternate
+#pragma unroll
+      for (int s = PARTS - 1; s >= 0; --s)
+#pragma unroll
+        for (int pa = 0; pa <= s; ++pa)
+#pragma unroll
+          for (int y = 0; y < TN; ++y)
+            acc[pl][x][y] = mfma_part(av[pa], bv[y][s - pa], acc[pl][x][y]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // A's group is fetched one k-tile ahead, under the products of the last two
+  // planes; registers hold no more (256 used, none spilled). B's is in flight
+  // while A's is converted. Issuing both at the top of the loop: (15,5,12)
+  // 0.31 against 0.28 ms, no difference on long sums.
+  float4 v[R][4];
+  load(0, v[0], nt > 1);
+  for (int t = 0; t < nt; ++t) {
+#pragma unroll
+    for (int r = 1; r < R; ++r) load(r, v[r], true);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) stash(r, v[r]);
+    __syncthreads();
+    multiply(0);
+    load(0, v[0], t + 2 < nt);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(1);
+    multiply(2);
+  }
+
+  const uint64_t maskA = SPLITK ? ((uint64_t)(M - 1) << d.n) : d.cmask;
+  const uint64_t maskB = ~maskA & ((1ull << (d.m + d.n)) - 1);
+  const float so =
+      !SPLITK && d.split_out == 2 ? split_out_scale(d, b, K, bm == 0 && bn == 0 && threadIdx.x == 0) : 1.f;
+  float2* Cc = SPLITK ? d.part + ((b << (d.k - d.kc_bits)) + chunk) * (M * N) : d.C + b * d.sC;
+  uint32_t* Cw = reinterpret_cast<uint32_t*>(Cc);
+  const int64_t row0 = bm * BM + wm * WM, col0 = bn * BN + wn * WN;
+  float vmax = 0.f;
+  auto put = [&](uint64_t addr, float re, float im) {
+    if (!SPLITK && d.split_out == 1)
+      store_split<true>(Cw, addr, re, im, 1.f);
+    else if (!SPLITK && d.split_out)
+      store_split<false>(Cw, addr, re, im, so);
+    else
+      Cc[addr] = make_float2(re, im);
+  };
+  const uint64_t pbase = pdep64((uint64_t)(row0 + 4 * h), maskA);
+  uint64_t pq[4], pg[4], pt[TM];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) pq[q] = pdep64((uint64_t)q, maskA);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) pg[g] = pdep64((uint64_t)(8 * g), maskA);
+#pragma unroll
+  for (int x = 0; x < TM; ++x) pt[x] = pdep64((uint64_t)(32 * x), maskA);
+  const bool rows4 = (maskA & 3) == 3;
+  constexpr float post = 1.f / (kUp * kUp);
+  bool odd = false;
+#pragma unroll
+  for (int y = 0; y < TN; ++y) {
+    const uint64_t pn = pdep64((uint64_t)(col0 + 32 * y + i), maskB);
+#pragma unroll
+    for (int x = 0; x < TM; ++x)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float vr[4], vi[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float p1 = acc[0][x][y][4 * g + q], p2 = acc[1][x][y][4 * g + q];
+          vr[q] = (p1 - p2) * post;
+          vi[q] = (acc[2][x][y][4 * g + q] - p1 - p2) * post;
+          vmax = fmaxf(vmax, fmaxf(fabsf(vr[q]), fabsf(vi[q])));
+          odd = odd || !isfinite(vr[q]) || !isfinite(vi[q]);
+        }
+        const uint64_t a0 = pbase | pt[x] | pg[g] | pn;
+        if (rows4) {
+          if (!SPLITK && d.split_out) {
+            uint32_t hw[4], lw[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              hw[q] = d.split_out == 1 ? split_pair<true>(vr[q], vi[q], 1.f, lw[q])
+                                       : split_pair<false>(vr[q], vi[q], so, lw[q]);
+            uint4* g4 = reinterpret_cast<uint4*>(Cw) + (a0 >> 2) * 2;
+            g4[0] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+            g4[1] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+          } else {
+            float4* c4 = reinterpret_cast<float4*>(Cc + a0);
+            c4[0] = make_float4(vr[0], vi[0], vr[1], vi[1]);
+            c4[1] = make_float4(vr[2], vi[2], vr[3], vi[3]);
+          }
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) put(a0 | pq[q], vr[q], vi[q]);
+        }
+      }
+  }
+  if (odd) {
+    // infinities, NaN, or a number too large for the scaled parts: this lane's
+    // outputs again, in FP32 from the operands
+    vmax = 0.f;
+    for (int e = 0; e < 16 * TM * TN; ++e) {
+      const int64_t row = wm * WM + 32 * (e / (16 * TN)) + 8 * ((e >> 2) & 3) + 4 * h + (e & 3);
+      const int64_t col = wn * WN + 32 * ((e >> 4) % TN) + i;
+      const float2 *a = A + row * K, *q = B + col * K;
+      float p1 = 0.f, p2 = 0.f, p3 = 0.f;
+      for (int64_t k = 0; k < KL; ++k) {
+        p1 = fmaf(a[k].x, q[k].x, p1);
+        p2 = fmaf(a[k].y, q[k].y, p2);
+        p3 = fmaf(a[k].x + a[k].y, q[k].x + q[k].y, p3);
+      }
+      const float re = p1 - p2, im = p3 - p1 - p2;
+      vmax = fmaxf(vmax, fmaxf(fabsf(re), fabsf(im)));
+      put(pdep64((uint64_t)(bm * BM + row), maskA) | pdep64((uint64_t)(bn * BN + col), maskB), re, im);
+    }
+  }
+  if (!SPLITK && d.scale_c) record_max(d.scale_c + b, vmax);
+}
+
+template <int BM, int BN, bool SPLITK>
+void run_parts(const GemmDesc& d, hipStream_t st) {
+  const int64_t chunks = SPLITK ? int64_t(1) << (d.k - d.kc_bits) : 1;
+  const int64_t blocks = ((int64_t(1) << d.m) / BM) * ((int64_t(1) << d.n) / BN) * d.nb * chunks;
+  hipLaunchKernelGGL((k_cgemm_parts<BM, BN, SPLITK>), dim3((unsigned)blocks), dim3(256), 0, st, d);
+}
+
+struct PartsCfg {
+  int bm, bn;
+  bool splitk;
+  const char* name;
+};
+const PartsCfg kParts[] = {
+    {128, 128, false, "parts_128x128x16"},
+    {128, 64, false, "parts_128x64x16"},
+    {128, 128, true, "splitk_parts_128x128x16"},
+    {128, 64, true, "splitk_parts_128x64x16"},
+};
+constexpr int kNumParts = sizeof(kParts) / sizeof(kParts[0]);
+
+}  // namespace
+
+int parts_config_count() { return kNumParts; }
+
+bool parts_config_fits(int cfg, int m, int k, int n) {
+  if (cfg < 0 || cfg >= kNumParts || m >= 40 || n >= 40) return false;
+  const PartsCfg& t = kParts[cfg];
+  const int c = t.splitk ? splitk_chunk_bits(m, k, n) : 0;
+  return (1ll << m) >= t.bm && (1ll << n) >= t.bn && k - c >= 4 && (!t.splitk || c > 0);
+}
+
+bool parts_config_splitk(int cfg) { return cfg >= 0 && cfg < kNumParts && kParts[cfg].splitk; }
+
+const char* parts_config_name(int cfg) { return cfg >= 0 && cfg < kNumParts ? kParts[cfg].name : "?"; }
+
+// A grid of at least one 128 x 128 tile per CU, or two 128 x 64 tiles: the
+// full tiles ((11,10,11), 256 tiles: 0.163 ms against 0.221 ms on the best
+// FP32 tile, (18,6,6): 0.081 against 0.085; with half a tile per CU,
+// (11,10,10): 0.136 against 0.124). Below that, a sum that can be split into
+// chunks for half a block per CU ((10,10,10): 0.065 against 0.076 ms,
+// (13,14,7): 0.55 against 0.90 on the best FP32 split-K tile; (7,12,7), 16
+// blocks: 0.053 against 0.029).
+int parts_config_default(int m, int k, int n, int64_t nb) {
+  if (m < 7 || n < 6 || m + n > 40) return -1;
+  const int wide = n >= 7;
+  const int64_t tiles = (int64_t(1) << (m + n - 13 - wide)) * nb;
+  const int full = wide ? 0 : 1, split = wide ? 2 : 3;
+  if (tiles >= (wide ? 256 : 512)) return parts_config_fits(full, m, k, n) ? full : -1;
+  return parts_config_fits(split, m, k, n) && (tiles << splitk_chunk_bits(m, k, n)) >= 128 ? split : -1;
+}
+
+void launch_cgemm_parts(const GemmDesc& d0, hipStream_t st) {
+  GemmDesc d = d0;
+  if (parts_config_splitk(d.cfg)) d.kc_bits = d.k - splitk_chunk_bits(d.m, d.k, d.n);
+  switch (d.cfg) {
+    case 0: run_parts<128, 128, false>(d, st); break;
+    case 1: run_parts<128, 64, false>(d, st); break;
+    case 2: run_parts<128, 128, true>(d, st); break;
+    case 3: run_parts<128, 64, true>(d, st); break;
+  }
+  if (parts_config_splitk(d.cfg)) launch_splitk_reduce(d, st);
+}
+
+}  // namespace ltn

@@ -195,6 +195,17 @@ const char* splitk_config_name(int cfg);
 int splitk_chunk_bits(int m, int k, int n);  // log2 of the number of chunks (0: not offered)
 int64_t splitk_part_elems(int m, int k, int n);  // partial elements per slice
 void launch_cgemm_splitk(const GemmDesc& d, hipStream_t st);
+// Second pass of a split-K product: the chunks' partials added into C.
+void launch_splitk_reduce(const GemmDesc& d, hipStream_t st);
+// The complex64 product from three bf16 parts of each real operand, formed
+// while the tiles are staged (k_parts.hip); full and split-K tiles.
+int parts_config_count();
+bool parts_config_fits(int cfg, int m, int k, int n);
+bool parts_config_splitk(int cfg);
+const char* parts_config_name(int cfg);
+// Untuned rule: the configuration to take for nb slices, or -1.
+int parts_config_default(int m, int k, int n, int64_t nb);
+void launch_cgemm_parts(const GemmDesc& d, hipStream_t st);
 // complex64 tensor X (2^rank per slice, rank >= 2) -> its split-layout
 // copy Y in the given split mode (fp16 scaled by the per-slice max slot[b]).
 void launch_split_convert(const float2* X, float2* Y, int rank, int nb, const uint32_t* slot,

@@ -50,15 +50,16 @@ struct ltn_plan_impl {
   // output), 1 = complex64 MFMA GEMM, 2 = split MFMA GEMM (cfg, swap),
   // 3 = narrow-step kernel (swap: rows taken from the B operand), 4 = split
   // sum over k for steps with few outputs, 5 = split-K complex64 MFMA GEMM
-  // (cfg, swap) for long sums with too few columns for a full tile
+  // (cfg, swap) for long sums with too few columns for a full tile, 6 =
+  // complex64 product from three bf16 parts (cfg, swap)
   struct Choice {
     int kind = 0, cfg = -1, swap = 0, tk = 1;
   };
   std::vector<Choice> choice[3];
   // adjoint products (forward-form GEMMs of the gradient sweep) by shape
   // (m | k << 8 | n << 16): kind 1 = a complex64 tile, kind 5 = a split-K
-  // tile (cfg, swap) chosen by ltn_autotune; absent = the fixed rule of
-  // enqueue_nt
+  // tile, kind 6 = a three-part tile (cfg, swap) chosen by ltn_autotune;
+  // absent = the fixed rule of enqueue_nt
   std::map<uint32_t, Choice> adj;
   std::vector<char> needs_grad;
   hipGraphExec_t graph[3] = {nullptr, nullptr, nullptr};
@@ -213,8 +214,9 @@ bool split_direct(ltn_plan* p, int t, int mode, bool gradarena) {
   if (T.producer < 0 || T.consumer < 0) return false;
   auto fused = [&](int s) { return r.fuse && p->step_group[s] >= 0; };
   if (fused(T.producer) || fused(T.consumer)) return false;
-  const int kp = r.choice[mode][T.producer].kind, kc = r.choice[mode][T.consumer].kind;
-  return (kp == 1 || kp == 2) && kc == 2;
+  const auto& pc = r.choice[mode][T.producer];
+  const bool writes = pc.kind == 1 || pc.kind == 2 || (pc.kind == 6 && !parts_config_splitk(pc.cfg));
+  return writes && r.choice[mode][T.consumer].kind == 2;
 }
 
 // The generic kernel's descriptor for forward step s.
@@ -358,7 +360,12 @@ void enqueue_step(ltn_plan* p, int s, int nb, bool gradarena, int mode) {
         d.scale_b = split_direct(p, rb, mode, gradarena) ? bound_slot(p, rb) : slot(p, rb);
       }
     }
-    launch_cgemm(d, ch.kind == 2 ? mode : LTN_C64, r.st);
+    if (ch.kind == 6) {
+      d.part = reinterpret_cast<float2*>(r.ws + r.lay.splitk);
+      launch_cgemm_parts(d, r.st);
+    } else {
+      launch_cgemm(d, ch.kind == 2 ? mode : LTN_C64, r.st);
+    }
   } else {
     GenericDesc g = step_generic_desc(p, s, nb, gradarena, mode);
     launch_generic(g, ch.tk, r.st);
@@ -694,8 +701,21 @@ void bind_state(ltn_plan* p, ltn_plan_impl* r, char* d_ws, size_t bytes, int gra
       ltn_plan_impl::Choice ch;
       ch.tk = default_tk(sp.k, (1ull << (sp.m + sp.n)) * (uint64_t)B);
       if (sp.kernel == LTN_K_MFMA) {
-        // MFMA columns follow the output's lowest bits when possible
+        // MFMA columns follow the output's lowest bits when possible.
+        // Gradient plans keep the FP32 tiles in their forward: a loss with the
+        // logarithm of small amplitudes magnifies any change of rounding
+        // there (3e-5 in the 20-qubit gradient, more than this path's own
+        // error on most inputs); their adjoint products do take the parts.
         bool nat = (sp.c_mask_a & 1) != 0;
+        if (mode == LTN_C64 && !grad)
+          for (bool sw : {nat, !nat}) {
+            const int c = ch.kind ? -1 : parts_config_default(sw ? sp.n : sp.m, sp.k, sw ? sp.m : sp.n, B);
+            if (c >= 0) {
+              ch.kind = 6;
+              ch.cfg = c;
+              ch.swap = sw;
+            }
+          }
         for (int kind : {mode == LTN_C64 ? 1 : 2, 1}) {
           int km = kind == 2 ? mode : LTN_C64;
           for (bool sw : {nat, !nat}) {
@@ -921,32 +941,13 @@ extern "C" ltn_status ltn_set_params(ltn_plan* p, const double* d_angles) {
 // One adjoint product in the forward form: C[merge(m, n)] = sum_k
 // X[m 2^k + k] Y[n 2^k + k] over a batch of nb slices, on the complex64
 // MFMA GEMM when a tile fits (either operand role), else the narrow kernel,
-// else the generic kernel.
+// else the generic kernel. Kinds: 1 a full FP32 tile, 5 a split-K tile (partials
+// in the workspace's split-K buffer, which the layout sizes for the adjoint
+// products of gradient plans), 6 a three-part tile.
 uint32_t adj_key(int m, int k, int n) { return (uint32_t)m | (uint32_t)k << 8 | (uint32_t)n << 16; }
 
 static void nt_gemm(ltn_plan* p, const float2* X, int64_t sX, const float2* Y, int64_t sY, float2* C,
-                    int64_t sC, int m, int k, int n, uint64_t cmask, int nb, int sw, int cfg) {
-  const uint64_t full = (m + n) >= 64 ? ~0ull : ((1ull << (m + n)) - 1);
-  GemmDesc d{};
-  d.A = sw ? Y : X;
-  d.B = sw ? X : Y;
-  d.C = C;
-  d.sA = sw ? sY : sX;
-  d.sB = sw ? sX : sY;
-  d.sC = sC;
-  d.m = sw ? n : m;
-  d.n = sw ? m : n;
-  d.k = k;
-  d.cmask = sw ? (~cmask & full) : cmask;
-  d.nb = nb;
-  d.cfg = cfg;
-  launch_cgemm(d, LTN_C64, p->rt->st);
-}
-
-// The same product on a split-K tile (partials in the workspace's split-K
-// buffer, which the layout sizes for the adjoint products of gradient plans).
-static void nt_splitk(ltn_plan* p, const float2* X, int64_t sX, const float2* Y, int64_t sY, float2* C,
-                      int64_t sC, int m, int k, int n, uint64_t cmask, int nb, int sw, int cfg) {
+                    int64_t sC, int m, int k, int n, uint64_t cmask, int nb, int kind, int sw, int cfg) {
   auto& r = *p->rt;
   const uint64_t full = (m + n) >= 64 ? ~0ull : ((1ull << (m + n)) - 1);
   GemmDesc d{};
@@ -963,7 +964,12 @@ static void nt_splitk(ltn_plan* p, const float2* X, int64_t sX, const float2* Y,
   d.nb = nb;
   d.cfg = cfg;
   d.part = reinterpret_cast<float2*>(r.ws + r.lay.splitk);
-  launch_cgemm_splitk(d, r.st);
+  if (kind == 1)
+    launch_cgemm(d, LTN_C64, r.st);
+  else if (kind == 5)
+    launch_cgemm_splitk(d, r.st);
+  else
+    launch_cgemm_parts(d, r.st);
 }
 
 static void enqueue_nt(ltn_plan* p, const float2* X, int64_t sX, const float2* Y, int64_t sY,
@@ -971,19 +977,23 @@ static void enqueue_nt(ltn_plan* p, const float2* X, int64_t sX, const float2* Y
   auto& r = *p->rt;
   const uint64_t full = (m + n) >= 64 ? ~0ull : ((1ull << (m + n)) - 1);
   const auto tuned = r.adj.find(adj_key(m, k, n));
-  if (tuned != r.adj.end() && tuned->second.kind == 1) {
-    nt_gemm(p, X, sX, Y, sY, C, sC, m, k, n, cmask, nb, tuned->second.swap, tuned->second.cfg);
+  if (tuned != r.adj.end() && tuned->second.kind > 0) {
+    const auto& t = tuned->second;
+    nt_gemm(p, X, sX, Y, sY, C, sC, m, k, n, cmask, nb, t.kind, t.swap, t.cfg);
     return;
   }
-  if (tuned != r.adj.end() && tuned->second.kind == 5) {
-    nt_splitk(p, X, sX, Y, sY, C, sC, m, k, n, cmask, nb, tuned->second.swap, tuned->second.cfg);
-    return;
+  for (int sw = 0; sw < 2; ++sw) {
+    const int cfg = parts_config_default(sw ? n : m, k, sw ? m : n, nb);
+    if (cfg >= 0) {
+      nt_gemm(p, X, sX, Y, sY, C, sC, m, k, n, cmask, nb, 6, sw, cfg);
+      return;
+    }
   }
   for (int sw = 0; sw < 2; ++sw) {
     const int mm = sw ? n : m, nn = sw ? m : n;
     const int cfg = default_cfg(mm, k, nn, LTN_C64);
     if (cfg >= 0 && mm >= 5 && nn >= 5) {
-      nt_gemm(p, X, sX, Y, sY, C, sC, m, k, n, cmask, nb, sw, cfg);
+      nt_gemm(p, X, sX, Y, sY, C, sC, m, k, n, cmask, nb, 1, sw, cfg);
       return;
     }
   }
@@ -1424,24 +1434,19 @@ void tune_adjoint(ltn_plan* p, std::map<std::string, std::pair<int, int>>& cache
       if (it != cache.end()) {
         const int kind = it->second.first >= 1000 ? it->second.first / 1000 : 0;
         const int cfg = it->second.first % 1000, sw = it->second.second;
-        if (kind == 1 && (sw ? gemm_config_fits(cfg, n, k, m, LTN_C64) : gemm_config_fits(cfg, m, k, n, LTN_C64))) {
-          pick.kind = 1;
-          pick.cfg = cfg;
-          pick.swap = sw;
-        } else if (kind == 5 && (sw ? splitk_config_fits(cfg, n, k, m) : splitk_config_fits(cfg, m, k, n))) {
-          pick.kind = 5;
+        const int rm = sw ? n : m, rn = sw ? m : n;
+        if ((kind == 1 && gemm_config_fits(cfg, rm, k, rn, LTN_C64)) ||
+            (kind == 5 && splitk_config_fits(cfg, rm, k, rn)) || (kind == 6 && parts_config_fits(cfg, rm, k, rn))) {
+          pick.kind = kind;
           pick.cfg = cfg;
           pick.swap = sw;
         }
       } else {
         auto run = [&](const Choice& c) {
-          if (c.kind == 1)
+          if (c.kind > 0) {
             nt_gemm(p, Xs, int64_t(1) << rc, Ys, int64_t(1) << other.rank, C, int64_t(1) << self.rank,
-                    m, k, n, cmask, r.B, c.swap, c.cfg);
-          else if (c.kind == 5)
-            nt_splitk(p, Xs, int64_t(1) << rc, Ys, int64_t(1) << other.rank, C, int64_t(1) << self.rank,
-                      m, k, n, cmask, r.B, c.swap, c.cfg);
-          else {
+                    m, k, n, cmask, r.B, c.kind, c.swap, c.cfg);
+          } else {
             r.adj.erase(key);
             enqueue_nt(p, Xs, int64_t(1) << rc, Ys, int64_t(1) << other.rank, C, int64_t(1) << self.rank,
                        m, k, n, cmask, r.B);
@@ -1462,6 +1467,15 @@ void tune_adjoint(ltn_plan* p, std::map<std::string, std::pair<int, int>>& cache
             if (sw ? splitk_config_fits(c, n, k, m) : splitk_config_fits(c, m, k, n)) {
               Choice ch;
               ch.kind = 5;
+              ch.cfg = c;
+              ch.swap = sw;
+              cands.push_back(ch);
+            }
+        for (int sw = 0; sw < 2; ++sw)
+          for (int c = 0; c < parts_config_count(); ++c)
+            if (sw ? parts_config_fits(c, n, k, m) : parts_config_fits(c, m, k, n)) {
+              Choice ch;
+              ch.kind = 6;
               ch.cfg = c;
               ch.swap = sw;
               cands.push_back(ch);
@@ -1505,6 +1519,7 @@ extern "C" ltn_status ltn_autotune(ltn_plan* p, int32_t mode, const char* cache_
     auto cache = read_cache(cache_path);
     bool dirty = false;
     using Choice = ltn_plan_impl::Choice;
+    const bool fp32_forward = r.grad && mode == LTN_C64;  // see bind_state
     auto encode = [](const Choice& c) {
       return c.kind > 0 ? std::make_pair(c.kind * 1000 + c.cfg, c.swap) : std::make_pair(-c.tk, 0);
     };
@@ -1581,6 +1596,15 @@ extern "C" ltn_status ltn_autotune(ltn_plan* p, int32_t mode, const char* cache_
             if (sw ? splitk_config_fits(c, sp.n, sp.k, sp.m) : splitk_config_fits(c, sp.m, sp.k, sp.n)) {
               Choice ch;
               ch.kind = 5;
+              ch.cfg = c;
+              ch.swap = sw;
+              cands.push_back(ch);
+            }
+        for (int sw = 0; sw < 2 && !fp32_forward; ++sw)
+          for (int c = 0; c < parts_config_count(); ++c)
+            if (sw ? parts_config_fits(c, sp.n, sp.k, sp.m) : parts_config_fits(c, sp.m, sp.k, sp.n)) {
+              Choice ch;
+              ch.kind = 6;
               ch.cfg = c;
               ch.swap = sw;
               cands.push_back(ch);
@@ -1701,6 +1725,11 @@ extern "C" ltn_status ltn_set_step_kernel(ltn_plan* p, int32_t step, int32_t mod
       c.kind = 5;
       c.cfg = cfg;
       c.swap = swap ? 1 : 0;
+    } else if (kind == 6) {
+      require(parts_config_fits(cfg, m, sp.k, n), "three-part tile configuration does not fit the step");
+      c.kind = 6;
+      c.cfg = cfg;
+      c.swap = swap ? 1 : 0;
     } else {
       require(false, "unknown kernel kind");
     }
@@ -1732,6 +1761,7 @@ extern "C" const char* ltn_kernel_name(int32_t kind, int32_t cfg, int32_t mode) 
     case 3: return cfg == 0 ? "narrow_tile" : (cfg == 1 ? "narrow_rows" : "?");
     case 4: return cfg == 0 ? "split_sum" : "?";
     case 5: return splitk_config_name(cfg);
+    case 6: return parts_config_name(cfg);
   }
   return "?";
 }
