@@ -61,8 +61,9 @@ enum {
  * with at least 8 contracted complex elements splits each real part of
  * both operands, scaled by an exact power of two, into hi + lo in fp16
  * (11 + 11 bits) or bf16 (8 + 8 bits) and sums hi*hi, hi*lo and lo*hi on
- * the matrix cores; the other steps stay complex64. Tensors stay complex64
- * in memory. */
+ * the matrix cores; the other steps stay complex64 (as do long sums with few
+ * outputs where the complex64 kernel is the faster one). Tensors stay
+ * complex64 in memory. */
 enum {
   LTN_C64 = 0,        /* complex64 GEMMs on FP32 MFMA / FP32 VALU, or on
                          bf16 MFMA with three parts that hold all 24 bits
@@ -509,7 +510,9 @@ ltn_status ltn_permute(const void* d_in, void* d_out, int32_t rank, const int32_
  * matrix cores, tiles down to 16 complex columns, FP32 partials added in
  * chunk order by a second pass), 6 = complex64 GEMM on bf16 MFMA: each real
  * operand as three bf16 parts whose sum is the FP32 value, the six largest
- * products of parts summed in FP32 (cfg 0, 1: full tiles; 2, 3: split-K);
+ * products of parts summed in FP32 (cfg 0, 1: full tiles; 2, 3: split-K), or
+ * in split fp16 mode as two scaled fp16 parts on sums of 2^10 and more (cfg 4:
+ * full, 5: split-K);
  * cfg = tile configuration of that
  * kind (-1 for the generic kernel); swap = operands exchanged (rows come
  * from B). Requires a bound plan. */

@@ -14,6 +14,16 @@
 // the error against complex128 is 0.84 of the FP32 tiles' at K = 2^10 and
 // 2^12 (6.9e-7 against 8.1e-7, 1.39e-6 against 1.62e-6).
 //
+// In the split fp16 mode the same kernel takes two fp16 parts of the operands
+// scaled per slice (11 + 11 bits and a sign, three products): 18 flops per
+// complex multiply-add against the 24 of the 2 x 2 real form, and operands read
+// as complex64, so nothing is converted before. Only sums of 2^10 and more take
+// it: there its error is the split tiles' (5.08e-7 against 5.07e-7 at 2^10,
+// 7.11e-7 against 7.15e-7 at 2^11, 1.00e-6 against 1.02e-6 at 2^12); on shorter
+// ones the rounded operand sums show (1.24e-7 against 1.05e-7 at 2^4). (13,12,11):
+// 1.17 ms against 1.39 on the best split tile, matrix cores 57 % busy at 1.78
+// GHz.
+//
 // What bounds it: power. At (13,12,11) the matrix cores are busy 66 % of the
 // cycles and the clock falls to 1.8 GHz; the same step takes 2.00 ms (275
 // TFLOP/s of 8 flops per complex multiply-add, 1.24 PFLOP/s executed; a large
@@ -39,6 +49,7 @@ namespace {
 
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 
 // The last part of a number below 2^-110 falls below bf16's smallest number.
 // Circuits have such entries (cos(pi/2) = 6e-17 and its products), so operands
@@ -47,31 +58,54 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // multiplications per wave and k-tile: 1-2 % of the time.
 constexpr float kUp = 0x1p24f;
 
-// Parts of eight FP32 values times kUp, as the operand words of one MFMA lane.
-__device__ __forceinline__ void to_parts(const float (&x)[8], u32x4 (&o)[3]) {
+// Parts of eight FP32 values times `up`, as the operand words of one MFMA lane.
+template <int PARTS>
+__device__ __forceinline__ void to_parts(const float (&x)[8], float up, u32x4 (&o)[PARTS]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    float a = x[2 * j] * kUp, b = x[2 * j + 1] * kUp;
+    float a = x[2 * j] * up, b = x[2 * j + 1] * up;
+    if constexpr (PARTS == 3) {
 #pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
-      o[p][j] = w;
-      a -= __uint_as_float(w << 16);
-      b -= __uint_as_float(w & 0xffff0000u);
+      for (int p = 0; p < 3; ++p) {
+        const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
+        o[p][j] = w;
+        a -= __uint_as_float(w << 16);
+        b -= __uint_as_float(w & 0xffff0000u);
+      }
+    } else {
+      const halfx2 h = __builtin_convertvector((floatx2){a, b}, halfx2);
+      o[0][j] = __builtin_bit_cast(uint32_t, h);
+      // (float)h exactly subtracted: one mixed-precision instruction each
+      const floatx2 r = {__builtin_fmaf((float)h.x, -1.f, a), __builtin_fmaf((float)h.y, -1.f, b)};
+      o[1][j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, halfx2));
     }
   }
 }
 
+template <int PARTS>
 __device__ __forceinline__ floatx16 mfma_part(u32x4 a, u32x4 b, floatx16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(SplitType<true>::V8, a),
-                                                 __builtin_bit_cast(SplitType<true>::V8, b), c, 0, 0, 0);
+  if constexpr (PARTS == 3)
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(SplitType<true>::V8, a),
+                                                   __builtin_bit_cast(SplitType<true>::V8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(SplitType<false>::V8, a),
+                                                  __builtin_bit_cast(SplitType<false>::V8, b), c, 0, 0, 0);
+}
+
+// Two fp16 parts: the operand's largest |Re|, |Im| goes to [2^13, 2^14), so that
+// Re + Im stays below 2^15
+__device__ __forceinline__ float fp16_up(uint32_t maxbits) {
+  const int e = (int)((maxbits >> 23) & 0xff);
+  if (e == 0 || e == 0xff) return 1.f;
+  const int se = 267 - e;
+  return __uint_as_float((uint32_t)(se > 254 ? 254 : se) << 23);
 }
 
 // SPLITK: block w takes chunk w / (tiles * nb) of the sum for tile w % (tiles *
 // nb) and writes its FP32 partial of C to part, as k_cgemm_c64's split-K form.
-template <int BM, int BN, bool SPLITK>
+template <int BM, int BN, int PARTS, bool SPLITK>
 __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
-  constexpr int T = 256, KT = 16, PARTS = 3, NWM = 2, NWN = 2;
+  constexpr int T = 256, KT = 16, NWM = 2, NWN = 2;
   constexpr int WM = BM / NWM, WN = BN / NWN, TM = WM / 32, TN = WN / 32;
   constexpr int ROWS = BM + BN, GRP = 2 * ROWS, R = (GRP + T - 1) / T;
   static_assert(TM >= 1 && TN >= 1 && GRP % 64 == 0, "tile too small");
@@ -89,6 +123,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   const int nt = (int)(KL / KT);
   const float2* A = d.A + b * d.sA + bm * BM * K + chunk * KL;
   const float2* B = d.B + b * d.sB + bn * BN * K + chunk * KL;
+  const float ua = PARTS == 3 ? kUp : fp16_up(d.scale_a[b]), ub = PARTS == 3 ? kUp : fp16_up(d.scale_b[b]);
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tid = threadIdx.x;
@@ -98,11 +133,13 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   // the groups of a tile may end within a round of the threads, between two waves
   auto has = [&](int r) { return GRP % T == 0 || r < R - 1 || T * r + 64 * wave < GRP; };
   const float4* src[R];
+  float up[R];
   int dst[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int c = tid + T * r, row = c >> 1, g = c & 1;
     src[r] = reinterpret_cast<const float4*>(row < BM ? A + row * K : B + (row - BM) * K) + g;
+    up[r] = PARTS == 3 ? kUp : (row < BM ? ua : ub);
     dst[r] = 2 * row + (g ^ ((row >> 3) & 1));
   }
   // one k-tile of group r, and on to the next tile (`more`: there is one)
@@ -125,15 +162,15 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) su[q] = re[q] + im[q];
     u32x4 o[PARTS];
-    to_parts(re, o);
+    to_parts<PARTS>(re, up[r], o);
 #pragma unroll
     for (int p = 0; p < PARTS; ++p) S[p][dst[r]] = o[p];
     __builtin_amdgcn_sched_barrier(0);
-    to_parts(im, o);
+    to_parts<PARTS>(im, up[r], o);
 #pragma unroll
     for (int p = 0; p < PARTS; ++p) S[PARTS + p][dst[r]] = o[p];
     __builtin_amdgcn_sched_barrier(0);
-    to_parts(su, o);
+    to_parts<PARTS>(su, up[r], o);
 #pragma unroll
     for (int p = 0; p < PARTS; ++p) S[2 * PARTS + p][dst[r]] = o[p];
     __builtin_amdgcn_sched_barrier(0);
@@ -168,7 +205,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
         for (int pa = 0; pa <= s; ++pa)
 #pragma unroll
           for (int y = 0; y < TN; ++y)
-            acc[pl][x][y] = mfma_part(av[pa], bv[y][s - pa], acc[pl][x][y]);
+            acc[pl][x][y] = mfma_part<PARTS>(av[pa], bv[y][s - pa], acc[pl][x][y]);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -217,7 +254,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
 #pragma unroll
   for (int x = 0; x < TM; ++x) pt[x] = pdep64((uint64_t)(32 * x), maskA);
   const bool rows4 = (maskA & 3) == 3;
-  constexpr float post = 1.f / (kUp * kUp);
+  const float post = 1.f / ua / ub;
   bool odd = false;
 #pragma unroll
   for (int y = 0; y < TN; ++y) {
@@ -233,7 +270,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
           vr[q] = (p1 - p2) * post;
           vi[q] = (acc[2][x][y][4 * g + q] - p1 - p2) * post;
           vmax = fmaxf(vmax, fmaxf(fabsf(vr[q]), fabsf(vi[q])));
-          odd = odd || !isfinite(vr[q]) || !isfinite(vi[q]);
+          if (PARTS == 3) odd = odd || !isfinite(vr[q]) || !isfinite(vi[q]);
         }
         const uint64_t a0 = pbase | pt[x] | pg[g] | pn;
         if (rows4) {
@@ -257,7 +294,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
         }
       }
   }
-  if (odd) {
+  if (PARTS == 3 && odd) {
     // infinities, NaN, or a number too large for the scaled parts: this lane's
     // outputs again, in FP32 from the operands
     vmax = 0.f;
@@ -279,65 +316,97 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   if (!SPLITK && d.scale_c) record_max(d.scale_c + b, vmax);
 }
 
-template <int BM, int BN, bool SPLITK>
+template <int BM, int BN, int PARTS, bool SPLITK>
 void run_parts(const GemmDesc& d, hipStream_t st) {
   const int64_t chunks = SPLITK ? int64_t(1) << (d.k - d.kc_bits) : 1;
   const int64_t blocks = ((int64_t(1) << d.m) / BM) * ((int64_t(1) << d.n) / BN) * d.nb * chunks;
-  hipLaunchKernelGGL((k_cgemm_parts<BM, BN, SPLITK>), dim3((unsigned)blocks), dim3(256), 0, st, d);
+  hipLaunchKernelGGL((k_cgemm_parts<BM, BN, PARTS, SPLITK>), dim3((unsigned)blocks), dim3(256), 0, st, d);
 }
 
 struct PartsCfg {
-  int bm, bn;
+  int bm, bn, parts;
   bool splitk;
   const char* name;
 };
 const PartsCfg kParts[] = {
-    {128, 128, false, "parts_128x128x16"},
-    {128, 64, false, "parts_128x64x16"},
-    {128, 128, true, "splitk_parts_128x128x16"},
-    {128, 64, true, "splitk_parts_128x64x16"},
+    {128, 128, 3, false, "parts_128x128x16"},
+    {128, 64, 3, false, "parts_128x64x16"},
+    {128, 128, 3, true, "splitk_parts_128x128x16"},
+    {128, 64, 3, true, "splitk_parts_128x64x16"},
+    // split fp16 mode only
+    {128, 128, 2, false, "parts2_128x128x16"},
+    {128, 128, 2, true, "splitk_parts2_128x128x16"},
 };
-constexpr int kNumParts = sizeof(kParts) / sizeof(kParts[0]);
+constexpr int kNumParts = sizeof(kParts) / sizeof(kParts[0]), kNumParts3 = 4;
+constexpr int kParts2MinK = 10;  // shorter sums: less exact than the split tiles
 
 }  // namespace
 
-int parts_config_count() { return kNumParts; }
+int parts_config_count(int mode) { return mode == LTN_SPLIT_F16 ? kNumParts : kNumParts3; }
 
-bool parts_config_fits(int cfg, int m, int k, int n) {
-  if (cfg < 0 || cfg >= kNumParts || m >= 40 || n >= 40) return false;
+bool parts_config_fits(int cfg, int m, int k, int n, int mode) {
+  if (cfg < 0 || cfg >= parts_config_count(mode) || m >= 40 || n >= 40) return false;
   const PartsCfg& t = kParts[cfg];
   const int c = t.splitk ? splitk_chunk_bits(m, k, n) : 0;
+  if (t.parts == 2 && k < kParts2MinK) return false;
   return (1ll << m) >= t.bm && (1ll << n) >= t.bn && k - c >= 4 && (!t.splitk || c > 0);
 }
 
 bool parts_config_splitk(int cfg) { return cfg >= 0 && cfg < kNumParts && kParts[cfg].splitk; }
 
-const char* parts_config_name(int cfg) { return cfg >= 0 && cfg < kNumParts ? kParts[cfg].name : "?"; }
+const char* parts_config_name(int cfg, int mode) {
+  return cfg >= 0 && cfg < parts_config_count(mode) ? kParts[cfg].name : "?";
+}
 
-// A grid of at least one 128 x 128 tile per CU, or two 128 x 64 tiles: the
-// full tiles ((11,10,11), 256 tiles: 0.163 ms against 0.221 ms on the best
-// FP32 tile, (18,6,6): 0.081 against 0.085; with half a tile per CU,
-// (11,10,10): 0.136 against 0.124). Below that, a sum that can be split into
-// chunks for half a block per CU ((10,10,10): 0.065 against 0.076 ms,
-// (13,14,7): 0.55 against 0.90 on the best FP32 split-K tile; (7,12,7), 16
-// blocks: 0.053 against 0.029).
-int parts_config_default(int m, int k, int n, int64_t nb) {
+// complex64: full tiles where two 128 x 128 tiles per CU can share it, or two
+// 128 x 64 tiles ((13,10,10), 512 tiles: 0.286 ms; (18,6,6): 0.081 against
+// 0.085 on the best FP32 tile); with one per CU, the split-K form on sums from
+// 2^11 ((13,11,9): 0.302 against 0.347, (11,12,11): 0.55 against 0.69) and
+// full tiles on shorter ones ((11,10,11): 0.163 against 0.177, FP32 0.221).
+// Fewer tiles: split-K where its chunks give half a block per CU ((10,10,10):
+// 0.065 against 0.076 ms on the best FP32 tile, (13,14,7): 0.55 against 0.90;
+// (7,12,7), 16 blocks: 0.053 against 0.029; full tiles, (11,10,10): 0.136
+// against 0.124).
+// split fp16: the two-part tiles on sums of 2^10 and more ((13,10,10): 0.168
+// against 0.207 ms on the best split tile, (13,12,11): 1.30 against 1.53), with
+// one tile per CU split-K from 2^12 ((11,12,11): 0.353 against 0.363, (13,11,9):
+// 0.210 against 0.198), with fewer from 2^11 ((10,12,10): 0.120 against 0.155,
+// (13,15,8): 1.38 against 2.67; at 2^10, (11,10,10): 0.086 against 0.074).
+// split bf16, and 64 columns in either split mode: the three-part split-K form
+// where a long sum leaves at most one 64 x 64 split tile per CU ((13,14,7) 0.59
+// against 1.16 ms, (14,13,6) 0.40 against 0.81; with two per CU, (12,13,9):
+// 0.59 against 0.51, and with a shorter sum, (10,12,10): 0.171 against 0.148).
+int parts_config_default(int m, int k, int n, int64_t nb, int mode) {
   if (m < 7 || n < 6 || m + n > 40) return -1;
-  const int wide = n >= 7;
-  const int64_t tiles = (int64_t(1) << (m + n - 13 - wide)) * nb;
-  const int full = wide ? 0 : 1, split = wide ? 2 : 3;
-  if (tiles >= (wide ? 256 : 512)) return parts_config_fits(full, m, k, n) ? full : -1;
-  return parts_config_fits(split, m, k, n) && (tiles << splitk_chunk_bits(m, k, n)) >= 128 ? split : -1;
+  const bool wide = n >= 7, f16 = mode == LTN_SPLIT_F16;
+  const int64_t outs = (int64_t(1) << (m + n)) * nb, tiles = outs >> (wide ? 14 : 13);
+  int full = -1, split = -1;
+  if (mode == LTN_C64) {
+    full = wide ? 0 : 1;
+    split = wide ? 2 : 3;
+  } else if (f16 && wide) {
+    full = 4;
+    split = k >= 11 ? 5 : -1;
+  } else if (k >= 13 && outs >> 12 <= 256) {
+    split = wide ? 2 : 3;
+  }
+  if (full >= 0 && parts_config_fits(full, m, k, n, mode) &&
+      (tiles >= 512 || (wide && tiles >= 256 && (k < (f16 ? 12 : 11) || !parts_config_fits(split, m, k, n, mode)))))
+    return full;
+  if (!parts_config_fits(split, m, k, n, mode) || (tiles << splitk_chunk_bits(m, k, n)) < 128) return -1;
+  return tiles < 512 ? split : -1;
 }
 
 void launch_cgemm_parts(const GemmDesc& d0, hipStream_t st) {
   GemmDesc d = d0;
   if (parts_config_splitk(d.cfg)) d.kc_bits = d.k - splitk_chunk_bits(d.m, d.k, d.n);
   switch (d.cfg) {
-    case 0: run_parts<128, 128, false>(d, st); break;
-    case 1: run_parts<128, 64, false>(d, st); break;
-    case 2: run_parts<128, 128, true>(d, st); break;
-    case 3: run_parts<128, 64, true>(d, st); break;
+    case 0: run_parts<128, 128, 3, false>(d, st); break;
+    case 1: run_parts<128, 64, 3, false>(d, st); break;
+    case 2: run_parts<128, 128, 3, true>(d, st); break;
+    case 3: run_parts<128, 64, 3, true>(d, st); break;
+    case 4: run_parts<128, 128, 2, false>(d, st); break;
+    case 5: run_parts<128, 128, 2, true>(d, st); break;
   }
   if (parts_config_splitk(d.cfg)) launch_splitk_reduce(d, st);
 }

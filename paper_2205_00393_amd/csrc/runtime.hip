@@ -168,15 +168,30 @@ float2* arena_ptr(ltn_plan* p, uint64_t off_bytes) {
   return reinterpret_cast<float2*>(r.ws + r.lay.arena + off_bytes * (uint64_t)r.B);
 }
 
-// Untuned complex64 tiles: the three-product tiles first, then the direct
-// tiles 0-7 (sums shorter than 16); split modes: in order.
-int default_cfg(int m, int k, int n, int mode) {
+// Untuned FP32 tiles: the three-product tiles first, then the direct tiles
+// 0-7 (sums shorter than 16).
+int default_cfg(int m, int k, int n) {
   static const int c64_order[] = {10, 15, 13, 0, 1, 2, 3, 4, 5, 6, 7};
-  if (mode == LTN_C64) {
-    for (int c : c64_order)
-      if (gemm_config_fits(c, m, k, n, mode)) return c;
-    return -1;
-  }
+  for (int c : c64_order)
+    if (gemm_config_fits(c, m, k, n, LTN_C64)) return c;
+  return -1;
+}
+
+// Untuned split tiles for nb slices. Sums of 64 and more: the DMA-staged
+// tiles, the largest of which every CU gets one ((13,12,11) fp16: 1.54 ms
+// against 1.65 on the register-staged 128 x 128 tile; (11,10,10), 256 tiles
+// of 128 x 64: 0.074 against 0.114; (10,10,10), 64 x 64: 0.056 against 0.107).
+// Shorter sums with many tiles write more than they multiply: the register-
+// staged 128 x 64 tile ((14,4,12): 0.113 against 0.118 for 128 x 128 and
+// 0.129 with DMA).
+int default_split_cfg(int m, int k, int n, int64_t nb, int mode) {
+  const int64_t outs = m + n > 40 ? int64_t(1) << 40 : (int64_t(1) << (m + n)) * nb;
+  const bool many = outs >> 14 >= 256, half = outs >> 13 >= 256;
+  static const int large[] = {10, 11, 12, 13}, middle[] = {11, 12, 13}, small_[] = {13}, brief[] = {1, 2, 3};
+  const int* order = k >= 6 ? (many ? large : half ? middle : small_) : (many ? brief : small_);
+  const int len = k >= 6 ? (many ? 4 : half ? 3 : 1) : (many ? 3 : 1);
+  for (int i = 0; i < len; ++i)
+    if (gemm_config_fits(order[i], m, k, n, mode)) return order[i];
   for (int c = 0; c < gemm_config_count(mode); ++c)
     if (gemm_config_fits(c, m, k, n, mode)) return c;
   return -1;
@@ -361,6 +376,10 @@ void enqueue_step(ltn_plan* p, int s, int nb, bool gradarena, int mode) {
       }
     }
     if (ch.kind == 6) {
+      if (f16) {
+        d.scale_a = slot(p, sw ? sp.b : sp.a);
+        d.scale_b = slot(p, sw ? sp.a : sp.b);
+      }
       d.part = reinterpret_cast<float2*>(r.ws + r.lay.splitk);
       launch_cgemm_parts(d, r.st);
     } else {
@@ -707,9 +726,9 @@ void bind_state(ltn_plan* p, ltn_plan_impl* r, char* d_ws, size_t bytes, int gra
         // there (3e-5 in the 20-qubit gradient, more than this path's own
         // error on most inputs); their adjoint products do take the parts.
         bool nat = (sp.c_mask_a & 1) != 0;
-        if (mode == LTN_C64 && !grad)
+        if (mode != LTN_C64 || !grad)
           for (bool sw : {nat, !nat}) {
-            const int c = ch.kind ? -1 : parts_config_default(sw ? sp.n : sp.m, sp.k, sw ? sp.m : sp.n, B);
+            const int c = ch.kind ? -1 : parts_config_default(sw ? sp.n : sp.m, sp.k, sw ? sp.m : sp.n, B, mode);
             if (c >= 0) {
               ch.kind = 6;
               ch.cfg = c;
@@ -717,9 +736,9 @@ void bind_state(ltn_plan* p, ltn_plan_impl* r, char* d_ws, size_t bytes, int gra
             }
           }
         for (int kind : {mode == LTN_C64 ? 1 : 2, 1}) {
-          int km = kind == 2 ? mode : LTN_C64;
           for (bool sw : {nat, !nat}) {
-            int c = sw ? default_cfg(sp.n, sp.k, sp.m, km) : default_cfg(sp.m, sp.k, sp.n, km);
+            const int m = sw ? sp.n : sp.m, n = sw ? sp.m : sp.n;
+            const int c = kind == 2 ? default_split_cfg(m, sp.k, n, B, mode) : default_cfg(m, sp.k, n);
             if (c >= 0 && ch.kind == 0) {
               ch.kind = kind;
               ch.cfg = c;
@@ -983,7 +1002,7 @@ static void enqueue_nt(ltn_plan* p, const float2* X, int64_t sX, const float2* Y
     return;
   }
   for (int sw = 0; sw < 2; ++sw) {
-    const int cfg = parts_config_default(sw ? n : m, k, sw ? m : n, nb);
+    const int cfg = parts_config_default(sw ? n : m, k, sw ? m : n, nb, LTN_C64);
     if (cfg >= 0) {
       nt_gemm(p, X, sX, Y, sY, C, sC, m, k, n, cmask, nb, 6, sw, cfg);
       return;
@@ -991,7 +1010,7 @@ static void enqueue_nt(ltn_plan* p, const float2* X, int64_t sX, const float2* Y
   }
   for (int sw = 0; sw < 2; ++sw) {
     const int mm = sw ? n : m, nn = sw ? m : n;
-    const int cfg = default_cfg(mm, k, nn, LTN_C64);
+    const int cfg = default_cfg(mm, k, nn);
     if (cfg >= 0 && mm >= 5 && nn >= 5) {
       nt_gemm(p, X, sX, Y, sY, C, sC, m, k, n, cmask, nb, 1, sw, cfg);
       return;
@@ -1436,7 +1455,7 @@ void tune_adjoint(ltn_plan* p, std::map<std::string, std::pair<int, int>>& cache
         const int cfg = it->second.first % 1000, sw = it->second.second;
         const int rm = sw ? n : m, rn = sw ? m : n;
         if ((kind == 1 && gemm_config_fits(cfg, rm, k, rn, LTN_C64)) ||
-            (kind == 5 && splitk_config_fits(cfg, rm, k, rn)) || (kind == 6 && parts_config_fits(cfg, rm, k, rn))) {
+            (kind == 5 && splitk_config_fits(cfg, rm, k, rn)) || (kind == 6 && parts_config_fits(cfg, rm, k, rn, LTN_C64))) {
           pick.kind = kind;
           pick.cfg = cfg;
           pick.swap = sw;
@@ -1472,8 +1491,8 @@ void tune_adjoint(ltn_plan* p, std::map<std::string, std::pair<int, int>>& cache
               cands.push_back(ch);
             }
         for (int sw = 0; sw < 2; ++sw)
-          for (int c = 0; c < parts_config_count(); ++c)
-            if (sw ? parts_config_fits(c, n, k, m) : parts_config_fits(c, m, k, n)) {
+          for (int c = 0; c < parts_config_count(LTN_C64); ++c)
+            if (sw ? parts_config_fits(c, n, k, m, LTN_C64) : parts_config_fits(c, m, k, n, LTN_C64)) {
               Choice ch;
               ch.kind = 6;
               ch.cfg = c;
@@ -1601,8 +1620,8 @@ extern "C" ltn_status ltn_autotune(ltn_plan* p, int32_t mode, const char* cache_
               cands.push_back(ch);
             }
         for (int sw = 0; sw < 2 && !fp32_forward; ++sw)
-          for (int c = 0; c < parts_config_count(); ++c)
-            if (sw ? parts_config_fits(c, sp.n, sp.k, sp.m) : parts_config_fits(c, sp.m, sp.k, sp.n)) {
+          for (int c = 0; c < parts_config_count(mode); ++c)
+            if (sw ? parts_config_fits(c, sp.n, sp.k, sp.m, mode) : parts_config_fits(c, sp.m, sp.k, sp.n, mode)) {
               Choice ch;
               ch.kind = 6;
               ch.cfg = c;
@@ -1726,7 +1745,7 @@ extern "C" ltn_status ltn_set_step_kernel(ltn_plan* p, int32_t step, int32_t mod
       c.cfg = cfg;
       c.swap = swap ? 1 : 0;
     } else if (kind == 6) {
-      require(parts_config_fits(cfg, m, sp.k, n), "three-part tile configuration does not fit the step");
+      require(parts_config_fits(cfg, m, sp.k, n, mode), "tile configuration does not fit the step");
       c.kind = 6;
       c.cfg = cfg;
       c.swap = swap ? 1 : 0;
@@ -1761,7 +1780,7 @@ extern "C" const char* ltn_kernel_name(int32_t kind, int32_t cfg, int32_t mode) 
     case 3: return cfg == 0 ? "narrow_tile" : (cfg == 1 ? "narrow_rows" : "?");
     case 4: return cfg == 0 ? "split_sum" : "?";
     case 5: return splitk_config_name(cfg);
-    case 6: return parts_config_name(cfg);
+    case 6: return parts_config_name(cfg, mode);
   }
   return "?";
 }

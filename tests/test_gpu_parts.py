@@ -73,8 +73,8 @@ def _plan(P, a, b, m, k, n, order):
     return plan, rows_cols
 
 
-def _tiles(P, plan, mode="c64"):
-    for cfg in range(4):
+def _tiles(P, plan, mode="c64", cfgs=range(4)):
+    for cfg in cfgs:
         for swap in (0, 1):
             try:
                 plan.set_step_kernel(0, mode, 6, cfg, swap, 1)
@@ -169,3 +169,54 @@ def test_parts_write_split_layout(torch, mode):
         assert err < (3e-6 if mode == "split_f16" else 3e-5)
         ran += 1
     assert ran >= 2
+
+
+@pytest.mark.parametrize("operands", ["normal", "wide", "sparse"])
+@pytest.mark.parametrize("m,k,n,order", [(7, 10, 7, "rows"), (8, 10, 7, "cols"), (7, 12, 8, "mixed")])
+def test_two_parts_within_analytic_bound(torch, m, k, n, order, operands):
+    """Split fp16 mode: tiles on two scaled fp16 parts, three real products.
+    x = h + l + e with |e| <= 2^-24 |x| + 2^-38 max|x| (l's own rounding; fp16's
+    smallest number under the scale that takes the maximum to [2^13, 2^14)), and
+    l l' <= 2^-24 |x y| left out: 3.1 2^-24 |x y| + 2^-36 max|x| max|y| per
+    product; 3 K products of parts in FP32 per real product. The norm-wise error
+    on normal operands is the split tiles' (1.05 for the spread of one draw).
+    "wide": magnitudes over 2^16 by row, 2^8 by column."""
+    import paper_2205_00393_amd as P
+    a, b = _operands(m, k, n, operands)
+    if operands == "wide":
+        rng = np.random.default_rng(5)
+        a *= (2.0 ** -rng.integers(0, 17, size=(1 << m, 1)) * 2.0 ** -20).astype(np.float32)
+        b *= (2.0 ** -rng.integers(0, 9, size=(1 << n, 1))).astype(np.float32)
+    plan, rows_cols = _plan(P, a, b, m, k, n, order)
+    A, B = a.astype(np.complex128), b.astype(np.complex128)
+    exact = A @ B.T
+    S1, S2 = np.abs(A.real) @ np.abs(B.real).T, np.abs(A.imag) @ np.abs(B.imag).T
+    S3 = (np.abs(A.real) + np.abs(A.imag)) @ (np.abs(B.real) + np.abs(B.imag)).T
+    K = 1 << k
+    floor = K * 2.0 ** -36 * np.abs(A).max() * np.abs(B).max()
+    plan.set_step_kernel(0, "split_f16", 2, 3, 0, 1)
+    base = rel_l2(rows_cols(plan.execute([0], mode="split_f16").cpu().numpy()), exact)
+    ran = 0
+    for name, cfg, swap in _tiles(P, plan, "split_f16", (4, 5)):
+        L = 3 * K + 256
+        d = rows_cols(plan.execute([0], mode="split_f16").cpu().numpy()) - exact
+        r_re = float((np.abs(d.real) / (1.5 * (L + 4) * U * (S1 + S2) + 2 * floor)).max())
+        r_im = float((np.abs(d.imag) / (1.5 * (L + 8) * U * (S1 + S2 + S3) + 6 * floor)).max())
+        err = float(np.linalg.norm(d) / np.linalg.norm(exact))
+        banner(f"two parts ({m},{k},{n}) {order} {operands} {name} swap {swap}: max err/bound re {r_re:.3f} "
+               f"im {r_im:.3f}, rel {err:.2e} (split tile {base:.2e})")
+        assert r_re <= 1.0 and r_im <= 1.0
+        if operands == "normal":
+            assert err <= 1.05 * base
+        ran += 1
+    assert ran == 4
+
+
+def test_two_parts_only_where_they_are_as_exact(torch):
+    """Sums below 2^10 and the other modes refuse the two-part tiles."""
+    import paper_2205_00393_amd as P
+    for k, mode in ((9, "split_f16"), (10, "split_bf16"), (10, "c64")):
+        a, b = _operands(7, k, 7, "normal")
+        plan, _ = _plan(P, a, b, 7, k, 7, "rows")
+        assert not list(_tiles(P, plan, mode, (4, 5)))
+        assert plan.execute([0], mode=mode).isfinite().all()
