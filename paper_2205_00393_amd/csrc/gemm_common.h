@@ -22,14 +22,6 @@ __device__ __forceinline__ uint64_t pdep64(uint64_t x, uint64_t mask) {
   return r;
 }
 
-// wave-wide max, then one atomic per wave: the largest |x| of a tensor slice
-// (non-negative floats order like their bit patterns)
-__device__ __forceinline__ void record_max(uint32_t* slot, float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  if ((threadIdx.x & 63) == 0) raise_max(slot, v);
-}
-
 // sigma = 2^(-floor(log2 max)), so that max * sigma lies in [1, 2)
 __device__ __forceinline__ float scale_of(uint32_t maxbits) {
   int e = (int)((maxbits >> 23) & 0xff);

@@ -334,7 +334,7 @@ __global__ __launch_bounds__(256, MINW) void k_cgemm_c64(GemmDesc d) {
         }
       }
   }
-  if (!SPLITK && d.scale_c) record_max(d.scale_c + b, vmax);
+  if (!SPLITK && d.scale_c) block_raise_max(d.scale_c + b, vmax, reinterpret_cast<float*>(As));
 }
 
 // Second pass of the split-K GEMM: C[b][merge(row, column)] = the chunks'
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(GemmDesc d) {
   }
   const uint64_t row = (uint64_t)e >> d.n, col = (uint64_t)e & ((1ull << d.n) - 1);
   d.C[b * d.sC + (pdep64(row, d.cmask) | pdep64(col, ~d.cmask & full))] = make_float2(re, im);
-  if (d.scale_c) record_max(d.scale_c + b, fmaxf(fabsf(re), fabsf(im)));
+  if (d.scale_c) block_raise_max(d.scale_c + b, fmaxf(fabsf(re), fabsf(im)));
 }
 
 

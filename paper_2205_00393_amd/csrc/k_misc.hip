@@ -22,14 +22,6 @@ __global__ void k_set_range(uint64_t* d, uint64_t base, int n) {
   if (i < n) d[i] = base + (uint64_t)i;
 }
 
-// wave-wide max, then one atomic per wave (non-negative floats order like
-// their bit patterns)
-__device__ __forceinline__ void record_max(uint32_t* slot, float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  if ((threadIdx.x & 63) == 0) raise_max(slot, v);
-}
-
 // one block per (chunk of kGatherChunk elements of a leaf, slice): chunks
 // are numbered leaf after leaf (desc[l].chunk0 = first chunk of leaf l);
 // when every leaf is one chunk, block x is leaf x, else a binary search
@@ -67,7 +59,7 @@ __global__ void k_gather(const GatherDesc* __restrict__ desc, int n_leaves, int6
     vmax = fmaxf(vmax, fmaxf(fabsf(v.x), fabsf(v.y)));
     dst[c] = v;
   }
-  if (scales) record_max(scales + g.tensor * (int64_t)bstride + b, vmax);
+  if (scales) block_raise_max(scales + g.tensor * (int64_t)bstride + b, vmax);
 }
 
 __device__ __forceinline__ uint64_t pdep(uint64_t x, uint64_t mask) {
@@ -426,16 +418,19 @@ __device__ __forceinline__ void generic_body(const GenericDesc& d, uint64_t blk,
     }
   }
   if (d.scale_out) {
-    // every lane is active again here: one atomic per wave if all lanes that
-    // hold a value share one slice, else one per lane
-    uint64_t b0 = __shfl(bcur, 0, 64);
-    bool same = __all(bcur == b0 || bcur == ~0ull);
-    if (same && b0 != ~0ull) {
-      float v = vcur;
-      for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-      if ((threadIdx.x & 63) == 0) raise_max(d.scale_out + b0, v);
-    } else if (!same && bcur != ~0ull && vcur > 0.f) {
-      raise_max(d.scale_out + bcur, vcur);
+    // every thread is here again: one atomic if all of the block that hold a
+    // value share its first slice, else one per wave whose lanes share one,
+    // else one per lane
+    const uint64_t first = (blk * per_block) >> (d.xb + d.yb);
+    if (__syncthreads_and(bcur == first || bcur == ~0ull)) {
+      block_raise_max(d.scale_out + first, vcur);
+    } else {
+      const uint64_t b0 = __shfl(bcur, 0, 64);
+      const bool same = __all(bcur == b0 || bcur == ~0ull);
+      if (same && b0 != ~0ull)
+        record_max(d.scale_out + b0, vcur);
+      else if (!same && bcur != ~0ull)
+        raise_max(d.scale_out + bcur, vcur);
     }
   }
 }

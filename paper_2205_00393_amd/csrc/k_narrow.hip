@@ -15,7 +15,7 @@
 //    and all n positions of C).
 // Tile-local maps are linear in the bits, so they are tables over 6-bit
 // halves (built per block). Optional per-slice max recording of |re|, |im|
-// for split-fp16 consumers, one atomic per wave.
+// for split-fp16 consumers, one atomic per block.
 #include "kernels.h"
 
 namespace ltn {
@@ -145,10 +145,7 @@ __global__ __launch_bounds__(256) void k_narrow(NarrowDesc d) {
       // to another slice (or there is none)
       const int64_t nx = it + gridDim.x;
       if (nx >= work || nx / tiles != b) {
-        float v = vmax;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-        if ((tid & 63) == 0) raise_max(d.scale_c + b, v);
+        block_raise_max(d.scale_c + b, vmax);
         vmax = 0.f;
       }
     }
@@ -198,10 +195,7 @@ __global__ __launch_bounds__(256) void k_narrow_rows(NarrowDesc d) {
     }
     if (b != b_loaded) {
       if (b_loaded >= 0 && d.scale_c) {
-        float v = vmax;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-        if ((tid & 63) == 0) raise_max(d.scale_c + b_loaded, v);
+        block_raise_max(d.scale_c + b_loaded, vmax);
         vmax = 0.f;
       }
       __syncthreads();  // the previous slice's B is no longer read
@@ -233,10 +227,7 @@ __global__ __launch_bounds__(256) void k_narrow_rows(NarrowDesc d) {
     }
   }
   if (d.scale_c && b_loaded >= 0) {
-    float v = vmax;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    if ((tid & 63) == 0) raise_max(d.scale_c + b_loaded, v);
+    block_raise_max(d.scale_c + b_loaded, vmax);
   }
 }
 

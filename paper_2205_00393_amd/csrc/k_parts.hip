@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
       put(pdep64((uint64_t)(bm * BM + row), maskA) | pdep64((uint64_t)(bn * BN + col), maskB), re, im);
     }
   }
-  if (!SPLITK && d.scale_c) record_max(d.scale_c + b, vmax);
+  if (!SPLITK && d.scale_c) block_raise_max(d.scale_c + b, vmax, reinterpret_cast<float*>(S));
 }
 
 template <int BM, int BN, int PARTS, bool SPLITK>

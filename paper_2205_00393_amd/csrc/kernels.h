@@ -19,6 +19,37 @@ __device__ __forceinline__ void raise_max(uint32_t* slot, float v) {
   if (v > 0.f && *reinterpret_cast<volatile uint32_t*>(slot) < bits) atomicMax(slot, bits);
 }
 
+// wave-wide max, then one atomic per wave: the largest |x| of a tensor slice
+// (non-negative floats order like their bit patterns)
+__device__ __forceinline__ void record_max(uint32_t* slot, float v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+  if ((threadIdx.x & 63) == 0) raise_max(slot, v);
+}
+
+// The same for the largest v of the block, every thread of which calls it. The
+// slots of a tensor's slices share cache lines, where atomics of all blocks
+// queue at 5 ns each: one a block instead of one a wave (64 slices of (7,2,7)
+// on 64 x 32 tiles: 0.028 -> 0.011 ms; 0.009 without maxima). `top`: 16 floats of
+// LDS that no thread needs any more. The split tiles, fewer and larger, keep
+// one a wave: 18 registers more cost the 64 x 64 ones 10 %.
+__device__ __forceinline__ void block_raise_max(uint32_t* slot, float v, float* top) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) top[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < (int)(blockDim.x + 63) / 64; ++w) v = fmaxf(v, top[w]);
+    raise_max(slot, v);
+  }
+}
+
+__device__ __forceinline__ void block_raise_max(uint32_t* slot, float v) {
+  __shared__ float top[16];
+  block_raise_max(slot, v, top);
+}
+
 constexpr int kMaxLeafRank = 32;
 
 // Gather of one leaf into its per-slice layout (Sec. 2.1.1: a sliced index
