@@ -33,6 +33,7 @@ SOURCES = [
     ("plan.cpp", "host"),
     ("runtime.hip", "hip"),
     ("k_misc.hip", "hip"),
+    ("k_small.hip", "hip"),
     ("k_mfma.hip", "hip"),
     ("k_parts.hip", "hip"),
     ("k_permute.hip", "hip"),

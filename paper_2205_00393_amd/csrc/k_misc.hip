@@ -353,9 +353,9 @@ template <int TK>
 __device__ __forceinline__ void generic_body(const GenericDesc& d, uint64_t blk, uint64_t nblk) {
   const int per_block = 256 / TK;
   const int lane = threadIdx.x % TK;
-  const uint64_t n_out = 1ull << (d.xb + d.yb);
+  const uint64_t n_out = 1ull << (d.xb() + d.yb());
   const uint64_t total = n_out * (uint64_t)d.nb;
-  const uint64_t zc = 1ull << d.zb;
+  const uint64_t zc = 1ull << d.zb();
   const uint64_t zstep = pdep((uint64_t)TK, d.pz), zstepq = pdep((uint64_t)TK, d.qz);
   const uint64_t z0p = pdep((uint64_t)lane, d.pz), z0q = pdep((uint64_t)lane, d.qz);
   // running max of the outputs this lane wrote, per slice (flushed with an
@@ -363,7 +363,7 @@ __device__ __forceinline__ void generic_body(const GenericDesc& d, uint64_t blk,
   uint64_t bcur = ~0ull;
   float vcur = 0.f;
   for (uint64_t g = blk * per_block + threadIdx.x / TK; g < total; g += nblk * per_block) {
-    uint64_t b = g >> (d.xb + d.yb);
+    uint64_t b = g >> (d.xb() + d.yb());
     uint64_t o = g & (n_out - 1);
     // o enumerates the output in linear order: recover x, y from its bits
     uint64_t omask = d.ox | d.oy;
@@ -387,9 +387,9 @@ __device__ __forceinline__ void generic_body(const GenericDesc& d, uint64_t blk,
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        if (d.conjQ) q[j].y = -q[j].y;
-        re += p[j].x * q[j].x - p[j].y * q[j].y;
-        im += p[j].x * q[j].y + p[j].y * q[j].x;
+        if (d.conjQ()) q[j].y = -q[j].y;
+        re += fmaf(p[j].x, q[j].x, -(p[j].y * q[j].y));
+        im += fmaf(p[j].y, q[j].x, p[j].x * q[j].y);
       }
     }
     if (TK > 1) {
@@ -401,12 +401,7 @@ __device__ __forceinline__ void generic_body(const GenericDesc& d, uint64_t blk,
     }
     if (lane == 0) {
       float2* O = d.out + b * d.sO + oaddr;
-      if (d.accumulate) {
-        float2 v = *O;
-        *O = make_float2(v.x + re, v.y + im);
-      } else {
-        *O = make_float2(re, im);
-      }
+      *O = make_float2(re, im);
     }
     if (d.scale_out && lane == 0) {
       if (b != bcur) {
@@ -421,7 +416,7 @@ __device__ __forceinline__ void generic_body(const GenericDesc& d, uint64_t blk,
     // every thread is here again: one atomic if all of the block that hold a
     // value share its first slice, else one per wave whose lanes share one,
     // else one per lane
-    const uint64_t first = (blk * per_block) >> (d.xb + d.yb);
+    const uint64_t first = (blk * per_block) >> (d.xb() + d.yb());
     if (__syncthreads_and(bcur == first || bcur == ~0ull)) {
       block_raise_max(d.scale_out + first, vcur);
     } else {
@@ -548,7 +543,7 @@ void launch_generic_multi(const GenericDesc* d_descs, int n, uint64_t max_outs, 
 }
 
 void launch_generic(const GenericDesc& d, int tk, hipStream_t st) {
-  uint64_t outs = (1ull << (d.xb + d.yb)) * (uint64_t)d.nb;
+  uint64_t outs = (1ull << (d.xb() + d.yb())) * (uint64_t)d.nb;
   switch (tk) {
     case 1:
       hipLaunchKernelGGL(k_generic<1>, dim3(grid_for(outs, 256)), dim3(256), 0, st, d);

@@ -85,11 +85,30 @@ struct GenericDesc {
   float2* out;
   int64_t sP, sQ, sO;    // per-slice strides (elements)
   uint64_t px, pz, qy, qz, ox, oy;
-  int32_t xb, yb, zb;    // bit counts
-  int32_t conjQ;
-  int32_t accumulate;    // add into out instead of overwrite
+  // bit counts of x, y, z and whether Q is conjugated, in one word (words of
+  // an array element load on the scalar unit, its bytes do not)
+  uint32_t shape;
+  // runs of small steps (launch_small_run): places of P, Q and out in LDS, + 1
+  // (0: none; an operand with a place and an address is copied there when the
+  // run starts); the form of its sums (small_op), the wave that takes the step,
+  // + 1 (0: the block), whether the block meets before it, and whether P, Q are
+  // leaves (then the address is that of the leaf's GatherDesc)
+  uint32_t places, plan;
   int32_t nb;            // slices
   uint32_t* scale_out;   // if set: record the output's per-slice max |x|
+  __host__ __device__ int xb() const { return shape & 255; }
+  __host__ __device__ int yb() const { return (shape >> 8) & 255; }
+  __host__ __device__ int zb() const { return (shape >> 16) & 255; }
+  __host__ __device__ bool conjQ() const { return (shape >> 24) & 1; }
+  __host__ __device__ int lp() const { return (int)(places & 0xffff) - 1; }
+  __host__ __device__ int lq() const { return (int)(places >> 16) - 1; }
+  __host__ __device__ int lo() const { return (int)(plan & 0xffff) - 1; }
+  __host__ __device__ int wave() const { return (int)((plan >> 16) & 15) - 1; }
+  __host__ __device__ int sums() const { return (plan >> 20) & 7; }
+  __host__ __device__ bool level_first() const { return (plan >> 23) & 1; }
+  __host__ __device__ int leafP() const { return (plan >> 24) & 1; }
+  __host__ __device__ int leafQ() const { return (plan >> 25) & 1; }
+  void set_shape(int x, int y, int z, bool conj) { shape = x | y << 8 | z << 16 | (conj ? 1u << 24 : 0u); }
 };
 
 void launch_set_ids(uint64_t* d_ids, const uint64_t* h_ids, int n, hipStream_t st);
@@ -116,6 +135,15 @@ void launch_generic(const GenericDesc& d, int tk, hipStream_t st);
 // max_outs: largest 2^(xb + yb) among them
 void launch_generic_multi(const GenericDesc* d_descs, int n, uint64_t max_outs, int nb, int tk,
                           hipStream_t st);
+
+// A run of n small steps (device array, in level order; all forward steps or
+// all adjoint products) as one launch: one block per slice, lds_elems complex64
+// of LDS; a descriptor's nb is the place of its address tables there, in
+// 16-bit words.
+int small_run_waves();
+int small_run_side();  // inputs above this size are `big`
+void launch_small_run(const GenericDesc* d_descs, int n, bool adjoint, bool big, int lds_elems,
+                      const float2* leafdata, const uint64_t* ids, int nb, hipStream_t st);
 
 // C[merge(m, n)] = sum_k A[m 2^k + k] B[n 2^k + k] on FP32 MFMA; the output
 // bit j comes from A's next free bit if (cmask >> j) & 1, else from B's.

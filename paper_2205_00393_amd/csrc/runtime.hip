@@ -6,6 +6,7 @@
 // device memory of its own (the caller's workspace holds leaf data,
 // descriptors, slice ids, the per-slice arenas and gradient accumulators).
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cstring>
 #include <fstream>
@@ -70,8 +71,11 @@ struct ltn_plan_impl {
   // gradient launch sequence: runs of independent generic contractions of
   // consecutive steps share one launch (descriptors in the workspace)
   struct GradItem {
-    int what = 0;  // 0: forward step, 1: generic run, 2: large adjoint step
-    int step = -1, off = 0, count = 0, tk = 1;
+    // 0: forward step, 1: independent generic steps in one launch, 2: large
+    // adjoint step, 3: fused group, 4: run of small steps (step 1: of adjoint
+    // products; tk 2: with large inputs)
+    int what = 0;
+    int step = -1, off = 0, count = 0, tk = 1, lds = 0;
     uint64_t max_outs = 0;
   };
   // forward kept in the gradient arena by the last ltn_execute (plan bound
@@ -83,8 +87,9 @@ struct ltn_plan_impl {
   bool gseq_valid = false;
   std::vector<GenericDesc> gseq_descs;
   std::vector<GradItem> gseq_fwd, gseq_bwd;
-  // forward launch sequence per mode (what 0: step, 1: generic run, 3: fused group)
-  bool fseq_valid[3] = {false, false, false};
+  // forward launch sequence per mode, and whether any leaf has to be gathered
+  // for it (runs of small steps read leaves where they lie)
+  bool fseq_valid[3] = {false, false, false}, fseq_gather[3] = {true, true, true};
   std::vector<GenericDesc> fseq_descs[3];
   std::vector<GradItem> fseq[3];
   std::vector<uint64_t> host_ids;
@@ -246,9 +251,7 @@ GenericDesc step_generic_desc(ltn_plan* p, int s, int nb, bool gradarena, int mo
   g.sP = int64_t(1) << ta.rank;
   g.sQ = int64_t(1) << tb.rank;
   g.sO = int64_t(1) << tc.rank;
-  g.xb = sp.m;
-  g.yb = sp.n;
-  g.zb = sp.k;
+  g.set_shape(sp.m, sp.n, sp.k, false);
   g.px = ((1ull << sp.m) - 1) << sp.k;
   g.pz = (1ull << sp.k) - 1;
   g.qy = ((1ull << sp.n) - 1) << sp.k;
@@ -427,6 +430,16 @@ void enqueue_group(ltn_plan* p, int g, int nb, int mode) {
   launch_fused(d, r.st);
 }
 
+// A launch of generic contractions (what 1 or 4) from descriptors in memory.
+void enqueue_generic(ltn_plan* p, const GenericDesc* dd, const ltn_plan_impl::GradItem& it, int nb) {
+  if (it.what == 4)
+    launch_small_run(dd + it.off, it.count, it.step == 1, it.tk == 2, it.lds,
+                     reinterpret_cast<const float2*>(p->rt->ws + p->rt->lay.leafdata),
+                     reinterpret_cast<const uint64_t*>(p->rt->ws + p->rt->lay.ids), nb, p->rt->st);
+  else
+    launch_generic_multi(dd + it.off, it.count, it.max_outs, nb, it.tk, p->rt->st);
+}
+
 void enqueue_forward(ltn_plan* p, int nb, bool gradarena, int mode) {
   auto& r = *p->rt;
   const GatherDesc* gd = reinterpret_cast<const GatherDesc*>(r.ws + (gradarena ? r.lay.gd_grad : r.lay.gd_fwd));
@@ -435,16 +448,17 @@ void enqueue_forward(ltn_plan* p, int nb, bool gradarena, int mode) {
     scales = reinterpret_cast<uint32_t*>(r.ws + r.lay.scales);
     launch_fill_zero(scales, al((size_t)r.B * p->tensors.size() * 4), r.st);
   }
-  launch_gather(gd, (int)p->leaves.size(), r.gather_chunks, r.max_leaf_elems,
-                reinterpret_cast<const float2*>(r.ws + r.lay.leafdata), arena_ptr(p, 0),
-                reinterpret_cast<const uint64_t*>(r.ws + r.lay.ids), nb, scales, r.B, r.st);
+  if (gradarena || !r.fseq_valid[mode] || r.fseq_gather[mode])
+    launch_gather(gd, (int)p->leaves.size(), r.gather_chunks, r.max_leaf_elems,
+                  reinterpret_cast<const float2*>(r.ws + r.lay.leafdata), arena_ptr(p, 0),
+                  reinterpret_cast<const uint64_t*>(r.ws + r.lay.ids), nb, scales, r.B, r.st);
   if (gradarena && r.gseq_valid) {
     const GenericDesc* dd = reinterpret_cast<const GenericDesc*>(r.ws + r.lay.gdesc);
     for (const auto& it : r.gseq_fwd) {
       if (it.what == 0)
         enqueue_step(p, it.step, nb, true, mode);
       else
-        launch_generic_multi(dd + it.off, it.count, it.max_outs, nb, it.tk, r.st);
+        enqueue_generic(p, dd, it, nb);
     }
     return;
   }
@@ -457,7 +471,7 @@ void enqueue_forward(ltn_plan* p, int nb, bool gradarena, int mode) {
       else if (it.what == 3)
         enqueue_group(p, it.step, nb, mode);
       else
-        launch_generic_multi(dd + it.off, it.count, it.max_outs, nb, it.tk, r.st);
+        enqueue_generic(p, dd, it, nb);
     }
     return;
   }
@@ -471,12 +485,233 @@ void enqueue_forward(ltn_plan* p, int nb, bool gradarena, int mode) {
   }
 }
 
-// Forward launch sequence of a mode: consecutive generic steps share one
-// launch unless one of them reads, or writes over, memory another one
-// writes or reads (the arena reuses memory once a tensor is dead, so the
-// test is on per-slice byte ranges, not tensor ids). Fused sub-paths keep
-// their launch at their last step. Descriptors (for the bound batch size)
-// are copied to the workspace here, outside any capture.
+// A generic contraction in a launch sequence: what it reads and writes (ids:
+// tensor t, or n_tensors + t for its cotangent; per-slice byte ranges of the
+// arena), the step whose contractions consume its output (-1: not one of this
+// sequence), and whether the output is needed in memory even so.
+struct SeqOp {
+  GenericDesc g;
+  int tk = 1, step = -1, consumer = -1;
+  int in[2] = {-1, -1}, out = -1;
+  struct Range {
+    uint64_t lo, hi;
+    bool meets(const Range& o) const { return lo < o.hi && o.lo < hi; }
+  } rin[2], rout;
+  bool keep = false;
+  const GatherDesc* leaf[2] = {nullptr, nullptr};  // device descriptor of an operand that is a leaf
+  int work() const { return g.xb() + g.yb() + g.zb(); }
+};
+
+// Runs of small steps: at most 2^15 multiply-adds a step (one block's work of
+// about a launch: 512 threads take 3.5 us), 64 KiB of LDS (two blocks per CU).
+// Up to 2^11 a step is one wave's when others share its level.
+constexpr int kRunWork = 15, kWaveWork = 11, kRunSteps = 96, kRunLds = 8192;
+
+// Plan ops[i .. j) as one run: levels by dependence, places in LDS by first fit
+// over the levels a tensor is needed in, waves. False when LDS does not hold it
+// or when a block could write memory that another block of the run still reads
+// (the arena reuses memory across tensors, whose slices then overlap; with one
+// slice there is one block, which has read its inputs before it writes).
+bool plan_run(const std::vector<SeqOp>& ops, int i, int j, int nb, std::vector<GenericDesc>& out, int& lds) {
+  const int n = j - i;
+  struct Place {
+    int off, size, from, to;
+  };
+  std::vector<Place> placed;
+  auto place = [&](int size, int from, int to) {
+    int off = 0;
+    for (bool moved = true; moved;) {
+      moved = false;
+      for (auto& q : placed)
+        if (q.from <= to && from <= q.to && off < q.off + q.size && q.off < off + size) {
+          off = q.off + q.size;
+          moved = true;
+        }
+    }
+    placed.push_back({off, size, from, to});
+    lds = std::max(lds, off + size);
+    return off;
+  };
+  std::vector<int> level(n, 1), last(n, 0);
+  std::vector<std::array<int, 2>> from(n, {-1, -1});  // producers inside the run
+  std::vector<char> ext(n, 1);
+  for (int k = 0; k < n; ++k) {
+    const SeqOp& o = ops[i + k];
+    for (int q = 0; q < 2; ++q)
+      for (int m = 0; m < k; ++m)
+        if (ops[i + m].out == o.in[q]) {
+          from[k][q] = m;
+          level[k] = std::max(level[k], level[m] + 1);
+        }
+    for (int q = 0; q < 2; ++q)
+      if (from[k][q] >= 0) last[from[k][q]] = std::max(last[from[k][q]], level[k]);
+  }
+  for (int k = 0; k < n; ++k)
+    for (int m = k + 1; m < n && !ops[i + k].keep; ++m)
+      if (ops[i + m].step == ops[i + k].consumer) ext[k] = 0;
+  for (int k = 0; k < n && nb > 1; ++k) {
+    if (!ext[k]) continue;
+    const auto& w = ops[i + k].rout;
+    for (int m = 0; m < n; ++m) {
+      if (m != k && ext[m] && w.meets(ops[i + m].rout)) return false;
+      for (int q = 0; q < 2; ++q)
+        if (from[m][q] < 0 && !ops[i + m].leaf[q] && w.meets(ops[i + m].rin[q])) return false;
+    }
+  }
+  lds = 0;
+  std::vector<std::array<int, 3>> at(n, {-1, -1, -1});
+  for (int k = 0; k < n; ++k) {
+    const GenericDesc& g = ops[i + k].g;
+    const int size[2] = {1 << (g.xb() + g.zb()), 1 << (g.yb() + g.zb())};
+    for (int q = 0; q < 2; ++q)
+      if (from[k][q] >= 0)
+        at[k][q] = at[from[k][q]][2];
+      else
+        at[k][q] = place(size[q], 0, level[k]);
+    if (last[k]) at[k][2] = place(1 << (g.xb() + g.yb()), level[k], last[k]);
+    if (lds > kRunLds) return false;
+  }
+  // address tables behind the tensors, 16 bits an entry
+  std::vector<int> table(n);
+  int words = 4 * lds;
+  for (int k = 0; k < n; ++k) {
+    const GenericDesc& g = ops[i + k].g;
+    table[k] = words;
+    words += (1 << g.xb()) + (1 << (g.conjQ() ? g.zb() : g.yb()));
+  }
+  lds = (words + 3) / 4;
+  if (lds > kRunLds) return false;
+  std::vector<int> order(n);
+  for (int k = 0; k < n; ++k) order[k] = k;
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return level[a] < level[b]; });
+  const int waves = small_run_waves();
+  for (int a = 0; a < n;) {
+    int e = a;
+    while (e < n && level[order[e]] == level[order[a]]) ++e;
+    int w = 0;
+    for (int x = a; x < e; ++x) {
+      const int k = order[x];
+      GenericDesc g = ops[i + k].g;
+      // a step of the block's own unless several share the level
+      const bool own = e - a >= 2 && ops[i + k].work() <= (e - a >= waves / 2 ? kWaveWork : 9);
+      if (from[k][0] >= 0) g.P = nullptr;
+      if (from[k][1] >= 0) g.Q = nullptr;
+      const SeqOp& o = ops[i + k];
+      if (o.leaf[0]) g.P = reinterpret_cast<const float2*>(o.leaf[0]);
+      if (o.leaf[1]) g.Q = reinterpret_cast<const float2*>(o.leaf[1]);
+      if (!ext[k]) {
+        g.out = nullptr;
+        g.scale_out = nullptr;  // only matrix-core consumers read the maxima
+      }
+      // the step's partial sums per output, one lane each while there are threads
+      const int tk = o.tk == 1 ? 0 : (o.tk == 8 ? 3 : 6);
+      const int sums = tk == 0 ? 0 : (tk == 3 ? 1 : 3) + (g.xb() + g.yb() + tk > (own ? 6 : 9));
+      g.nb = table[k];
+      g.places = (uint32_t)(at[k][0] + 1) | (uint32_t)(at[k][1] + 1) << 16;
+      g.plan = (uint32_t)(at[k][2] + 1) | (own ? (uint32_t)(w++ % waves) + 1u : 0u) << 16 | (uint32_t)sums << 20 |
+               (x == a ? 1u << 23 : 0u) | (o.leaf[0] ? 1u << 24 : 0u) | (o.leaf[1] ? 1u << 25 : 0u);
+      out.push_back(g);
+    }
+    a = e;
+  }
+  return true;
+}
+
+// Launches of consecutive generic contractions: runs of small steps where two
+// or more fit one, else launches of independent steps (a step joins the launch
+// unless it reads, or writes over, what a member writes, or writes over what a
+// member reads).
+void sequence_generic(const std::vector<SeqOp>& ops, int nb, std::vector<GenericDesc>& descs,
+                      std::vector<ltn_plan_impl::GradItem>& seq) {
+  using Item = ltn_plan_impl::GradItem;
+  std::vector<const SeqOp*> group;
+  auto flush = [&]() {
+    for (int tk : {1, 8, 64}) {
+      Item it;
+      it.what = 1;
+      it.tk = tk;
+      it.off = (int)descs.size();
+      for (auto* e : group)
+        if (e->tk == tk) {
+          descs.push_back(e->g);
+          it.max_outs = std::max<uint64_t>(it.max_outs, 1ull << (e->g.xb() + e->g.yb()));
+        }
+      it.count = (int)descs.size() - it.off;
+      if (it.count) seq.push_back(it);
+    }
+    group.clear();
+  };
+  const int n = (int)ops.size();
+  for (int i = 0; i < n;) {
+    int j = i;
+    while (j < n && j - i < kRunSteps && ops[j].work() <= kRunWork) ++j;
+    std::vector<GenericDesc> run;
+    int lds = 0;
+    while (j - i >= 2) {
+      // contractions of one step (the two of an adjoint step) stay together
+      if (j == n || ops[j].step != ops[j - 1].step) {
+        run.clear();
+        if (plan_run(ops, i, j, nb, run, lds)) break;
+      }
+      j -= std::max(1, (j - i) / 16);
+    }
+    if (j - i >= 2) {
+      flush();
+      Item it;
+      it.what = 4;
+      it.off = (int)descs.size();
+      it.count = j - i;
+      it.lds = lds;
+      it.step = run[0].conjQ() ? 1 : 0;
+      for (auto& g : run) {
+        const int p = g.P ? 1 << (g.xb() + g.zb()) : 0, q = g.Q ? 1 << (g.yb() + g.zb()) : 0;
+        if (std::max(p, q) > small_run_side()) it.tk = 2;
+      }
+      descs.insert(descs.end(), run.begin(), run.end());
+      seq.push_back(it);
+      i = j;
+      continue;
+    }
+    const SeqOp& o = ops[i++];
+    bool clash = false;
+    for (auto* e : group)
+      clash = clash || e->rout.meets(o.rin[0]) || e->rout.meets(o.rin[1]) || e->rout.meets(o.rout) ||
+              e->rin[0].meets(o.rout) || e->rin[1].meets(o.rout);
+    if (clash) flush();
+    group.push_back(&o);
+  }
+  flush();
+}
+
+SeqOp step_seq_op(ltn_plan* p, int s, bool gradarena, int mode) {
+  const StepPlan& sp = p->steps[s];
+  SeqOp o;
+  o.g = step_generic_desc(p, s, p->rt->B, gradarena, mode);
+  o.tk = p->rt->choice[mode][s].tk;
+  o.step = s;
+  o.consumer = p->tensors[sp.out].consumer;
+  o.keep = gradarena;  // the adjoint sweep reads it
+  auto range = [&](int t) {
+    const TensorPlan& T = p->tensors[t];
+    const uint64_t off = gradarena ? T.goff : T.off;
+    return SeqOp::Range{off, off + T.bytes()};
+  };
+  const int in[2] = {sp.a, sp.b};
+  for (int q = 0; q < 2; ++q) {
+    o.in[q] = in[q];
+    o.rin[q] = range(in[q]);
+    // a run reads leaves where they lie; the adjoint sweep wants them gathered
+    if (in[q] < p->L && !gradarena)
+      o.leaf[q] = reinterpret_cast<const GatherDesc*>(p->rt->ws + p->rt->lay.gd_fwd) + in[q];
+  }
+  o.out = sp.out;
+  o.rout = range(sp.out);
+  return o;
+}
+
+// Forward launch sequence of a mode. Fused sub-paths keep their launch at
+// their last step. Descriptors (for the bound batch size) are copied to the
+// workspace here, outside any capture.
 void build_fwd_seq(ltn_plan* p, int mode) {
   auto& r = *p->rt;
   using Item = ltn_plan_impl::GradItem;
@@ -484,64 +719,31 @@ void build_fwd_seq(ltn_plan* p, int mode) {
   auto& descs = r.fseq_descs[mode];
   seq.clear();
   descs.clear();
-  struct Range {
-    uint64_t lo, hi;
-  };
-  auto range = [&](int t) { return Range{p->tensors[t].off, p->tensors[t].off + p->tensors[t].bytes()}; };
-  auto overlap = [](Range a, Range b) { return a.lo < b.hi && b.lo < a.hi; };
-  std::vector<std::pair<GenericDesc, int>> run;
-  std::vector<Range> reads, writes;
-  auto flush = [&]() {
-    for (int tk : {1, 8, 64}) {
-      Item it;
-      it.what = 1;
-      it.tk = tk;
-      it.off = (int)descs.size();
-      for (auto& e : run)
-        if (e.second == tk) {
-          descs.push_back(e.first);
-          it.max_outs = std::max<uint64_t>(it.max_outs, 1ull << (e.first.xb + e.first.yb));
-        }
-      it.count = (int)descs.size() - it.off;
-      if (it.count) seq.push_back(it);
-    }
-    run.clear();
-    reads.clear();
-    writes.clear();
+  std::vector<SeqOp> ops;
+  auto single = [&](int what, int step) {
+    sequence_generic(ops, r.B, descs, seq);
+    ops.clear();
+    Item it;
+    it.what = what;
+    it.step = step;
+    seq.push_back(it);
   };
   for (int s = 0; s < (int)p->steps.size(); ++s) {
-    const StepPlan& sp = p->steps[s];
     const int g = p->step_group[s];
     if (g >= 0 && r.fuse) {
-      if (s == p->groups[g].st.back().step) {
-        flush();
-        Item it;
-        it.what = 3;
-        it.step = g;
-        seq.push_back(it);
-      }
-      continue;
+      if (s == p->groups[g].st.back().step) single(3, g);
+    } else if (r.choice[mode][s].kind != 0) {
+      single(0, s);
+    } else {
+      ops.push_back(step_seq_op(p, s, false, mode));
     }
-    const auto& ch = r.choice[mode][s];
-    if (ch.kind != 0) {
-      flush();
-      Item it;
-      it.what = 0;
-      it.step = s;
-      seq.push_back(it);
-      continue;
-    }
-    const Range ra = range(sp.a), rb = range(sp.b), rc = range(sp.out);
-    bool clash = false;
-    for (auto& w : writes) clash = clash || overlap(w, ra) || overlap(w, rb) || overlap(w, rc);
-    for (auto& q : reads) clash = clash || overlap(q, rc);
-    if (clash) flush();
-    run.push_back({step_generic_desc(p, s, r.B, false, mode), ch.tk});
-    reads.push_back(ra);
-    reads.push_back(rb);
-    writes.push_back(rc);
   }
-  flush();
+  sequence_generic(ops, r.B, descs, seq);
+  int from_leaves = 0;  // leaf operands that runs read themselves
+  for (const Item& it : seq)
+    for (int i = 0; i < it.count && it.what == 4; ++i)
+      from_leaves += descs[it.off + i].leafP() + descs[it.off + i].leafQ();
+  r.fseq_gather[mode] = from_leaves < (int)p->leaves.size();
   require(descs.size() <= p->steps.size(), "forward descriptor area too small");
   if (!descs.empty()) {
     char* dst = r.ws + r.lay.fdesc + (size_t)mode * p->steps.size() * sizeof(GenericDesc);
@@ -608,7 +810,9 @@ void launch_captured(ltn_plan* p, hipGraphExec_t& exec, hipGraph_t& src, F&& enq
 void run_batch(ltn_plan* p, int nb, int mode, double* out) {
   auto& r = *p->rt;
   if (!r.fseq_valid[mode]) build_fwd_seq(p, mode);
-  if (nb == r.B) {
+  // a graph pays from a handful of launches (one launch: 3 us directly, 10 us
+  // as a graph)
+  if (nb == r.B && r.fseq[mode].size() > 3) {
     launch_captured(p, r.graph[mode], r.graph_src[mode], [&] { enqueue_forward(p, nb, false, mode); });
   } else {
     enqueue_forward(p, nb, false, mode);
@@ -1057,9 +1261,7 @@ static void enqueue_nt(ltn_plan* p, const float2* X, int64_t sX, const float2* Y
   g.sP = sX;
   g.sQ = sY;
   g.sO = sC;
-  g.xb = m;
-  g.yb = n;
-  g.zb = k;
+  g.set_shape(m, n, k, false);
   g.px = ((1ull << m) - 1) << k;
   g.pz = (1ull << k) - 1;
   g.qy = ((1ull << n) - 1) << k;
@@ -1095,18 +1297,15 @@ static GenericDesc adj_generic_desc(ltn_plan* p, int s, int which, int nb, int* 
   GenericDesc g{};
   g.P = arena_ptr(p, tc.gcot);
   g.sP = int64_t(1) << tc.rank;
-  g.yb = sp.k;
   g.qy = (1ull << sp.k) - 1;
   g.oy = (1ull << sp.k) - 1;
-  g.conjQ = 1;
   g.nb = nb;
   if (which == 0) {
     g.Q = arena_ptr(p, tb.goff);
     g.out = arena_ptr(p, ta.gcot);
     g.sQ = int64_t(1) << tb.rank;
     g.sO = int64_t(1) << ta.rank;
-    g.xb = sp.m;
-    g.zb = sp.n;
+    g.set_shape(sp.m, sp.k, sp.n, true);
     g.px = cm;
     g.pz = ~cm & full;
     g.qz = ((1ull << sp.n) - 1) << sp.k;
@@ -1117,8 +1316,7 @@ static GenericDesc adj_generic_desc(ltn_plan* p, int s, int which, int nb, int* 
     g.out = arena_ptr(p, tb.gcot);
     g.sQ = int64_t(1) << ta.rank;
     g.sO = int64_t(1) << tb.rank;
-    g.xb = sp.n;
-    g.zb = sp.m;
+    g.set_shape(sp.n, sp.k, sp.m, true);
     g.px = ~cm & full;
     g.pz = cm;
     g.qz = ((1ull << sp.m) - 1) << sp.k;
@@ -1194,10 +1392,10 @@ static void enqueue_backward(ltn_plan* p, int nb) {
   if (r.gseq_valid) {
     const GenericDesc* dd = reinterpret_cast<const GenericDesc*>(r.ws + r.lay.gdesc);
     for (const auto& it : r.gseq_bwd) {
-      if (it.what == 1)
-        launch_generic_multi(dd + it.off, it.count, it.max_outs, nb, it.tk, r.st);
-      else
+      if (it.what == 2)
         enqueue_adjoint_step(p, it.step, nb);
+      else
+        enqueue_generic(p, dd, it, nb);
     }
   } else {
     for (int s = (int)p->steps.size() - 1; s >= 0; --s) enqueue_adjoint_step(p, s, nb);
@@ -1206,61 +1404,41 @@ static void enqueue_backward(ltn_plan* p, int nb) {
                              arena_ptr(p, 0), dids, nb, lg, r.st);
 }
 
-// Gradient launch sequence. The gradient arena gives every tensor and every
-// cotangent a place of its own, so consecutive generic contractions can
-// share one launch as long as none of them reads what another one writes:
-// forward, a step that consumes a tensor the run produces starts a new run;
-// backward (reverse order), a step whose output cotangent the run writes
-// does. Other kernels keep their place between the runs. The descriptors
-// (for the bound batch size; the launch passes the actual one) are copied
-// to the workspace here, outside any capture.
+// Gradient launch sequences: the recomputed forward (outputs of small steps
+// are kept in memory, where the adjoint sweep reads them) and the adjoint sweep
+// in reverse order. The gradient arena gives every tensor and every cotangent
+// a place of its own, so memory is never reused. The descriptors (for the
+// bound batch size; the launch passes the actual one) are copied to the
+// workspace here, outside any capture.
 static void build_grad_seq(ltn_plan* p) {
   auto& r = *p->rt;
   using Item = ltn_plan_impl::GradItem;
   r.gseq_descs.clear();
   r.gseq_fwd.clear();
   r.gseq_bwd.clear();
-  std::vector<std::pair<GenericDesc, int>> run;
-  std::vector<char> written(p->tensors.size(), 0);
-  std::vector<int> wlist;
-  auto flush = [&](std::vector<Item>& seq) {
-    for (int tk : {1, 8, 64}) {
-      Item it;
-      it.what = 1;
-      it.tk = tk;
-      it.off = (int)r.gseq_descs.size();
-      for (auto& e : run)
-        if (e.second == tk) {
-          r.gseq_descs.push_back(e.first);
-          it.max_outs = std::max<uint64_t>(it.max_outs, 1ull << (e.first.xb + e.first.yb));
-        }
-      it.count = (int)r.gseq_descs.size() - it.off;
-      if (it.count) seq.push_back(it);
-    }
-    run.clear();
-    for (int t : wlist) written[t] = 0;
-    wlist.clear();
-  };
+  std::vector<SeqOp> ops;
   auto single = [&](std::vector<Item>& seq, int what, int s) {
-    flush(seq);
+    sequence_generic(ops, r.B, r.gseq_descs, seq);
+    ops.clear();
     Item it;
     it.what = what;
     it.step = s;
     seq.push_back(it);
   };
   for (int s = 0; s < (int)p->steps.size(); ++s) {
-    const StepPlan& sp = p->steps[s];
-    const auto& ch = r.choice[LTN_C64][s];
-    if (ch.kind != 0) {
+    if (r.choice[LTN_C64][s].kind != 0)
       single(r.gseq_fwd, 0, s);
-      continue;
-    }
-    if (written[sp.a] || written[sp.b]) flush(r.gseq_fwd);
-    run.push_back({step_generic_desc(p, s, r.B, true, LTN_C64), ch.tk});
-    written[sp.out] = 1;
-    wlist.push_back(sp.out);
+    else
+      ops.push_back(step_seq_op(p, s, true, LTN_C64));
   }
-  flush(r.gseq_fwd);
+  sequence_generic(ops, r.B, r.gseq_descs, r.gseq_fwd);
+  ops.clear();
+  const int nt = (int)p->tensors.size();
+  auto range = [&](int t, bool cot) {
+    const TensorPlan& T = p->tensors[t];
+    const uint64_t off = cot ? T.gcot : T.goff;
+    return SeqOp::Range{off, off + T.bytes()};
+  };
   for (int s = (int)p->steps.size() - 1; s >= 0; --s) {
     const StepPlan& sp = p->steps[s];
     if (!r.needs_grad[sp.out]) continue;
@@ -1268,17 +1446,23 @@ static void build_grad_seq(ltn_plan* p) {
       single(r.gseq_bwd, 2, s);
       continue;
     }
-    if (written[sp.out]) flush(r.gseq_bwd);
     for (int which = 0; which < 2; ++which) {
-      const int t = which ? sp.b : sp.a;
+      const int t = which ? sp.b : sp.a, other = which ? sp.a : sp.b;
       if (!r.needs_grad[t]) continue;
-      int tk = 1;
-      run.push_back({adj_generic_desc(p, s, which, r.B, &tk), tk});
-      written[t] = 1;
-      wlist.push_back(t);
+      SeqOp o;
+      o.g = adj_generic_desc(p, s, which, r.B, &o.tk);
+      o.step = s;
+      o.consumer = p->tensors[t].producer;
+      o.in[0] = nt + sp.out;
+      o.rin[0] = range(sp.out, true);
+      o.in[1] = other;
+      o.rin[1] = range(other, false);
+      o.out = nt + t;
+      o.rout = range(t, true);
+      ops.push_back(o);
     }
   }
-  flush(r.gseq_bwd);
+  sequence_generic(ops, r.B, r.gseq_descs, r.gseq_bwd);
   require(r.gseq_descs.size() <= 3 * p->steps.size(), "gradient descriptor area too small");
   if (!r.gseq_descs.empty())
     HIPCHECK(hipMemcpyAsync(r.ws + r.lay.gdesc, r.gseq_descs.data(), r.gseq_descs.size() * sizeof(GenericDesc),
@@ -1589,6 +1773,10 @@ extern "C" ltn_status ltn_autotune(ltn_plan* p, int32_t mode, const char* cache_
       std::vector<Choice> cands;
       if (it != cache.end()) {
         cands.push_back(decode(it->second));
+      } else if (sp.m + sp.k + sp.n <= kWaveWork && r.choice[mode][s].kind == 0) {
+        // one launch of such a step takes its launch's 10 us on any kernel; in a
+        // run it is one wave's microsecond
+        cands.push_back(r.choice[mode][s]);
       } else {
         for (int kind : {2, 1}) {
           if (kind == 2 && mode == LTN_C64) continue;
