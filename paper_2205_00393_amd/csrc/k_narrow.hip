@@ -16,6 +16,8 @@
 // Tile-local maps are linear in the bits, so they are tables over 6-bit
 // halves (built per block). Optional per-slice max recording of |re|, |im|
 // for split-fp16 consumers, one atomic per block.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace ltn {
@@ -157,41 +159,46 @@ __device__ __forceinline__ uint64_t madd_n(uint64_t a, uint64_t d, uint64_t mask
   return ((a | ~mask) + d) & mask;
 }
 
-// Rows form: one thread per row of A. A block takes 256 consecutive rows
-// of one slice at a time; each thread issues the K / 2 16-byte loads of its
-// row (contiguous) at once, multiplies by B (N x K, broadcast from LDS) and
-// writes its N outputs. The output address of row r, column j is
-// pdep(chunk, cmask) | pdep(thread, cmask) | pdep(j, ~cmask): the first
-// part is advanced from chunk to chunk by a masked add, the second is fixed
-// per thread, the third is a table.
-template <int K, int N>
+// Rows form: U rows of A per thread. A block takes 256 U consecutive rows of one
+// slice at a time; each thread issues the 16-byte loads of its rows (K / 2 each,
+// contiguous; 256 rows apart) at once, multiplies by B (N x K, broadcast from
+// LDS) and writes its outputs. The output address of row r, column j is
+// pdep(chunk, cmask) | pdep(u, cmask) | pdep(thread, cmask) | pdep(j, ~cmask):
+// the first part is advanced from chunk to chunk by a masked add, the second is
+// uniform, the third fixed per thread, the last a table.
+// Bound by HBM: 4.6-5.6 TB/s of reads and writes from 2^26 bytes on (a copy: 4.9).
+template <int K, int N, int U>
 __global__ __launch_bounds__(256) void k_narrow_rows(NarrowDesc d) {
+  constexpr int kRows = 256 * U;
   __shared__ float2 Bs[N * K];
-  __shared__ uint64_t pj[N];
+  __shared__ uint64_t pj[N], pu[U];
   const int tid = threadIdx.x;
   const uint64_t full = (d.m + d.n) >= 64 ? ~0ull : ((1ull << (d.m + d.n)) - 1);
   if (tid < N) pj[tid] = pdep_n((uint64_t)tid, ~d.cmask & full);
+  if (tid >= 64 && tid < 64 + U) pu[tid - 64] = pdep_n((uint64_t)(tid - 64) << 8, d.cmask);
   const uint64_t pt = pdep_n((uint64_t)tid, d.cmask);
-  const int64_t R = int64_t(1) << d.m;
-  const int64_t chunks = (R >> 8) * d.nb;
-  const uint64_t step = pdep_n((uint64_t)gridDim.x << 8, d.cmask);
+  const int64_t chunks = ((int64_t(1) << d.m) / kRows) * d.nb;
+  const uint64_t step = pdep_n((uint64_t)gridDim.x * kRows, d.cmask);
   int64_t b_loaded = -1, r_prev = -1;
   uint64_t base = 0;
   float vmax = 0.f;
   for (int64_t c = blockIdx.x; c < chunks; c += gridDim.x) {
-    const int64_t b = (c << 8) >> d.m;
-    const int64_t r0 = (c << 8) - (b << d.m);
+    const int64_t b = (c * kRows) >> d.m;
+    const int64_t r0 = c * kRows - (b << d.m);
     const float2* Ar = d.A + b * d.sA + (r0 + tid) * K;
-    float2 a[K];
-    if constexpr (K >= 2) {
+    float2 a[U][K];
 #pragma unroll
-      for (int kp = 0; kp < K / 2; ++kp) {
-        const float4 v = reinterpret_cast<const float4*>(Ar)[kp];
-        a[2 * kp] = make_float2(v.x, v.y);
-        a[2 * kp + 1] = make_float2(v.z, v.w);
+    for (int u = 0; u < U; ++u) {
+      if constexpr (K >= 2) {
+#pragma unroll
+        for (int kp = 0; kp < K / 2; ++kp) {
+          const float4 v = reinterpret_cast<const float4*>(Ar + u * 256 * K)[kp];
+          a[u][2 * kp] = make_float2(v.x, v.y);
+          a[u][2 * kp + 1] = make_float2(v.z, v.w);
+        }
+      } else {
+        a[u][0] = Ar[u * 256];
       }
-    } else {
-      a[0] = Ar[0];
     }
     if (b != b_loaded) {
       if (b_loaded >= 0 && d.scale_c) {
@@ -208,22 +215,32 @@ __global__ __launch_bounds__(256) void k_narrow_rows(NarrowDesc d) {
       base = r0 > r_prev ? madd_n(base, step, d.cmask) : pdep_n((uint64_t)r0, d.cmask);
     }
     r_prev = r0;
-    float2 acc[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) acc[j] = make_float2(0.f, 0.f);
+    for (int u = 0; u < U; ++u) {
+      float2 acc[N];
 #pragma unroll
-    for (int kk = 0; kk < K; ++kk)
+      for (int j = 0; j < N; ++j) acc[j] = make_float2(0.f, 0.f);
 #pragma unroll
-      for (int j = 0; j < N; ++j) {
-        const float2 bv = Bs[j * K + kk];
-        acc[j].x += a[kk].x * bv.x - a[kk].y * bv.y;
-        acc[j].y += a[kk].x * bv.y + a[kk].y * bv.x;
+      for (int kk = 0; kk < K; ++kk)
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+          const float2 bv = Bs[j * K + kk];
+          acc[j].x += a[u][kk].x * bv.x - a[u][kk].y * bv.y;
+          acc[j].y += a[u][kk].x * bv.y + a[u][kk].y * bv.x;
+        }
+      float2* Cb = d.C + b * d.sC + (base | pt | pu[u]);
+      if (N >= 2 && !(d.cmask & 1)) {
+        // columns 2 j and 2 j + 1 are neighbours
+#pragma unroll
+        for (int j = 0; j < N; j += 2)
+          *reinterpret_cast<float4*>(Cb + pj[j]) =
+              make_float4(acc[j].x, acc[j].y, acc[j + 1 & (N - 1)].x, acc[j + 1 & (N - 1)].y);
+      } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j) Cb[pj[j]] = acc[j];
       }
-    float2* Cb = d.C + b * d.sC + (base | pt);
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      Cb[pj[j]] = acc[j];
-      vmax = fmaxf(vmax, fmaxf(fabsf(acc[j].x), fabsf(acc[j].y)));
+      for (int j = 0; j < N; ++j) vmax = fmaxf(vmax, fmaxf(fabsf(acc[j].x), fabsf(acc[j].y)));
     }
   }
   if (d.scale_c && b_loaded >= 0) {
@@ -231,14 +248,32 @@ __global__ __launch_bounds__(256) void k_narrow_rows(NarrowDesc d) {
   }
 }
 
+// U rows give a thread 128 bytes to read or write: 2^24 elements of (24,0,0) take
+// 0.046 ms, with U = 1 0.075 (blocks of 2 KiB are gone before their loads are
+// back); (23,1,1) 0.046 and 0.063, (22,2,2) 0.048 and 0.056. From K N = 32 on a row
+// has the loads already, and two rows' products crowd the registers ((21,3,3): 0.123
+// against 0.058). Fewer than 256 such blocks leave CUs idle.
+template <int K, int N>
+void launch_rows_kn(const NarrowDesc& d, hipStream_t st) {
+  constexpr int U = K * N <= 16 ? 16 / (K > N ? K : N) : 1;
+  const int64_t rows = (int64_t(1) << d.m) * d.nb;
+  const auto grid = [&](int u) { return dim3((unsigned)std::min<int64_t>(rows / (256 * u), 8192)); };
+  if constexpr (U > 1)
+    if ((int64_t(1) << d.m) >= 256 * U && rows >= 256 * 256 * U) {
+      hipLaunchKernelGGL((k_narrow_rows<K, N, U>), grid(U), dim3(256), 0, st, d);
+      return;
+    }
+  hipLaunchKernelGGL((k_narrow_rows<K, N, 1>), grid(1), dim3(256), 0, st, d);
+}
+
 template <int K>
-void launch_rows_k(const NarrowDesc& d, dim3 grid, hipStream_t st) {
+void launch_rows_k(const NarrowDesc& d, hipStream_t st) {
   switch (d.n) {
-    case 0: hipLaunchKernelGGL((k_narrow_rows<K, 1>), grid, dim3(256), 0, st, d); break;
-    case 1: hipLaunchKernelGGL((k_narrow_rows<K, 2>), grid, dim3(256), 0, st, d); break;
-    case 2: hipLaunchKernelGGL((k_narrow_rows<K, 4>), grid, dim3(256), 0, st, d); break;
-    case 3: hipLaunchKernelGGL((k_narrow_rows<K, 8>), grid, dim3(256), 0, st, d); break;
-    default: hipLaunchKernelGGL((k_narrow_rows<K, 16>), grid, dim3(256), 0, st, d); break;
+    case 0: launch_rows_kn<K, 1>(d, st); break;
+    case 1: launch_rows_kn<K, 2>(d, st); break;
+    case 2: launch_rows_kn<K, 4>(d, st); break;
+    case 3: launch_rows_kn<K, 8>(d, st); break;
+    default: launch_rows_kn<K, 16>(d, st); break;
   }
 }
 
@@ -248,17 +283,26 @@ bool narrow_fits(int m, int k, int n) { return k + n <= 10 && n <= 6 && m >= 0 &
 
 bool narrow_rows_fits(int m, int k, int n) { return k >= 0 && k <= 4 && n >= 0 && n <= 4 && m >= 8 && m <= 40; }
 
+// The rows form reads A straight into registers and has no barriers: 2^24 outputs
+// of (22,2,2) 0.048 ms against the tiles' 0.061, 256 slices of (12,4,2) 0.033
+// against 0.054, (17,2,2) 0.008 against 0.010. Tiles, which order their writes in
+// LDS, where a row's 8 outputs are neighbours in C (64 bytes a lane: (21,3,3)
+// 0.065 against 0.069, with maxima of one slice 0.081 against 0.072) and where
+// rows does not fit.
+int narrow_config_default(int m, int k, int n, uint64_t cmask) {
+  if (narrow_rows_fits(m, k, n) && (n != 3 || (cmask & 1))) return 1;
+  return narrow_fits(m, k, n) ? 0 : -1;
+}
+
 void launch_narrow(const NarrowDesc& d0, hipStream_t st) {
   NarrowDesc d = d0;
   if (d.cfg == 1) {
-    const int64_t chunks = ((int64_t(1) << d.m) >> 8) * d.nb;
-    const dim3 grid((unsigned)(chunks < 8192 ? chunks : 8192));
     switch (d.k) {
-      case 0: launch_rows_k<1>(d, grid, st); break;
-      case 1: launch_rows_k<2>(d, grid, st); break;
-      case 2: launch_rows_k<4>(d, grid, st); break;
-      case 3: launch_rows_k<8>(d, grid, st); break;
-      default: launch_rows_k<16>(d, grid, st); break;
+      case 0: launch_rows_k<1>(d, st); break;
+      case 1: launch_rows_k<2>(d, st); break;
+      case 2: launch_rows_k<4>(d, st); break;
+      case 3: launch_rows_k<8>(d, st); break;
+      default: launch_rows_k<16>(d, st); break;
     }
     return;
   }

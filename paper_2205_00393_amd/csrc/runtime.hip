@@ -983,10 +983,12 @@ void bind_state(ltn_plan* p, ltn_plan_impl* r, char* d_ws, size_t bytes, int gra
       }
       // steps with many output rows and no MFMA tile: the narrow kernel
       if (ch.kind == 0 && sp.m + sp.n >= 12) {
-        bool sw = sp.n > sp.m;
-        if (sw ? narrow_fits(sp.n, sp.k, sp.m) : narrow_fits(sp.m, sp.k, sp.n)) {
+        const bool sw = sp.n > sp.m;
+        const int c = sw ? narrow_config_default(sp.n, sp.k, sp.m, ~sp.c_mask_a)
+                         : narrow_config_default(sp.m, sp.k, sp.n, sp.c_mask_a);
+        if (c >= 0) {
           ch.kind = 3;
-          ch.cfg = 0;
+          ch.cfg = c;
           ch.swap = sw;
         }
       }
@@ -1237,7 +1239,8 @@ static void enqueue_nt(ltn_plan* p, const float2* X, int64_t sX, const float2* Y
   }
   if (m + n >= 12) {
     const bool sw = n > m;
-    if (sw ? narrow_fits(n, k, m) : narrow_fits(m, k, n)) {
+    const int cfg = narrow_config_default(sw ? n : m, k, sw ? m : n, sw ? ~cmask : cmask);
+    if (cfg >= 0) {
       NarrowDesc d{};
       d.A = sw ? Y : X;
       d.B = sw ? X : Y;
@@ -1250,6 +1253,7 @@ static void enqueue_nt(ltn_plan* p, const float2* X, int64_t sX, const float2* Y
       d.k = k;
       d.cmask = sw ? (~cmask & full) : cmask;
       d.nb = nb;
+      d.cfg = cfg;
       launch_narrow(d, r.st);
       return;
     }
