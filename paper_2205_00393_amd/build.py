@@ -34,6 +34,7 @@ SOURCES = [
     ("runtime.hip", "hip"),
     ("k_misc.hip", "hip"),
     ("k_small.hip", "hip"),
+    ("k_rowsum.hip", "hip"),
     ("k_mfma.hip", "hip"),
     ("k_parts.hip", "hip"),
     ("k_permute.hip", "hip"),

@@ -136,6 +136,19 @@ void launch_generic(const GenericDesc& d, int tk, hipStream_t st);
 void launch_generic_multi(const GenericDesc* d_descs, int n, uint64_t max_outs, int nb, int tk,
                           hipStream_t st);
 
+// out[X(x) | Y(y)] = sum_z P[X(x) | Z(z)] Q[Y(y) | Z(z)] for few y (k_rowsum.hip)
+struct RowsumDesc {
+  const float2 *P, *Q;
+  float2* out;
+  int64_t sP, sQ, sO;
+  uint64_t px, pz, qy, qz, ox, oy;  // address bits of x, y, z
+  uint64_t tile;                    // P's address bits inside a tile
+  int32_t xb, yb, zb, xt, zt;       // bit counts; rows and sum elements of a tile
+  int32_t nb, conj_p, conj_q;
+};
+bool rowsum_fits(const GenericDesc& g, RowsumDesc& d);  // fills d
+void launch_rowsum(const RowsumDesc& d, hipStream_t st);
+
 // A run of n small steps (device array, in level order; all forward steps or
 // all adjoint products) as one launch: one block per slice, lds_elems complex64
 // of LDS; a descriptor's nb is the place of its address tables there, in

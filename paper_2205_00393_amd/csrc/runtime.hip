@@ -13,6 +13,7 @@
 #include <map>
 #include <mutex>
 #include <sstream>
+#include <unordered_map>
 
 #include "kernels.h"
 #include "plan.h"
@@ -505,51 +506,57 @@ struct SeqOp {
 // Runs of small steps: at most 2^15 multiply-adds a step (one block's work of
 // about a launch: 512 threads take 3.5 us), 64 KiB of LDS (two blocks per CU).
 // Up to 2^11 a step is one wave's when others share its level.
+// Adjoint steps from 2^13 multiply-adds on take k_rowsum where it fits: 256 slices
+// of (6,2,6) 13 us a product, 25 in a launch of several generic ones; between 2^11
+// and 2^14 the line makes no difference.
+constexpr int kRowsumWork = 13;
 constexpr int kRunWork = 15, kWaveWork = 11, kRunSteps = 96, kRunLds = 8192;
 
 // Plan ops[i .. j) as one run: levels by dependence, places in LDS by first fit
 // over the levels a tensor is needed in, waves. False when LDS does not hold it
 // or when a block could write memory that another block of the run still reads
-// (the arena reuses memory across tensors, whose slices then overlap; with one
-// slice there is one block, which has read its inputs before it writes).
-bool plan_run(const std::vector<SeqOp>& ops, int i, int j, int nb, std::vector<GenericDesc>& out, int& lds) {
+// (`shared`: the arena reuses memory across tensors, whose slices then overlap;
+// not with one slice, where the one block has read its inputs before it writes).
+bool plan_run(const std::vector<SeqOp>& ops, int i, int j, bool shared, std::vector<GenericDesc>& out, int& lds) {
   const int n = j - i;
   struct Place {
     int off, size, from, to;
   };
   std::vector<Place> placed;
+  // the lowest gap among those placed (in order of place) that are needed at
+  // the same time
   auto place = [&](int size, int from, int to) {
     int off = 0;
-    for (bool moved = true; moved;) {
-      moved = false;
-      for (auto& q : placed)
-        if (q.from <= to && from <= q.to && off < q.off + q.size && q.off < off + size) {
-          off = q.off + q.size;
-          moved = true;
-        }
+    for (const Place& q : placed) {
+      if (q.from > to || from > q.to) continue;
+      if (off + size <= q.off) break;
+      off = std::max(off, q.off + q.size);
     }
-    placed.push_back({off, size, from, to});
+    placed.insert(std::upper_bound(placed.begin(), placed.end(), off,
+                                   [](int o, const Place& q) { return o < q.off; }),
+                  {off, size, from, to});
     lds = std::max(lds, off + size);
     return off;
   };
   std::vector<int> level(n, 1), last(n, 0);
   std::vector<std::array<int, 2>> from(n, {-1, -1});  // producers inside the run
   std::vector<char> ext(n, 1);
+  std::unordered_map<int, int> made, step_of;
   for (int k = 0; k < n; ++k) {
     const SeqOp& o = ops[i + k];
     for (int q = 0; q < 2; ++q)
-      for (int m = 0; m < k; ++m)
-        if (ops[i + m].out == o.in[q]) {
-          from[k][q] = m;
-          level[k] = std::max(level[k], level[m] + 1);
-        }
+      if (auto it = made.find(o.in[q]); it != made.end()) {
+        from[k][q] = it->second;
+        level[k] = std::max(level[k], level[it->second] + 1);
+      }
     for (int q = 0; q < 2; ++q)
       if (from[k][q] >= 0) last[from[k][q]] = std::max(last[from[k][q]], level[k]);
+    made[o.out] = k;
+    step_of[o.step] = k;
   }
   for (int k = 0; k < n; ++k)
-    for (int m = k + 1; m < n && !ops[i + k].keep; ++m)
-      if (ops[i + m].step == ops[i + k].consumer) ext[k] = 0;
-  for (int k = 0; k < n && nb > 1; ++k) {
+    if (auto it = step_of.find(ops[i + k].consumer); !ops[i + k].keep && it != step_of.end() && it->second > k) ext[k] = 0;
+  for (int k = 0; k < n && shared; ++k) {
     if (!ext[k]) continue;
     const auto& w = ops[i + k].rout;
     for (int m = 0; m < n; ++m) {
@@ -621,7 +628,7 @@ bool plan_run(const std::vector<SeqOp>& ops, int i, int j, int nb, std::vector<G
 // or more fit one, else launches of independent steps (a step joins the launch
 // unless it reads, or writes over, what a member writes, or writes over what a
 // member reads).
-void sequence_generic(const std::vector<SeqOp>& ops, int nb, std::vector<GenericDesc>& descs,
+void sequence_generic(const std::vector<SeqOp>& ops, bool shared, std::vector<GenericDesc>& descs,
                       std::vector<ltn_plan_impl::GradItem>& seq) {
   using Item = ltn_plan_impl::GradItem;
   std::vector<const SeqOp*> group;
@@ -645,16 +652,27 @@ void sequence_generic(const std::vector<SeqOp>& ops, int nb, std::vector<Generic
   for (int i = 0; i < n;) {
     int j = i;
     while (j < n && j - i < kRunSteps && ops[j].work() <= kRunWork) ++j;
-    std::vector<GenericDesc> run;
-    int lds = 0;
-    while (j - i >= 2) {
-      // contractions of one step (the two of an adjoint step) stay together
-      if (j == n || ops[j].step != ops[j - 1].step) {
-        run.clear();
-        if (plan_run(ops, i, j, nb, run, lds)) break;
+    // the longest run, by bisection; contractions of one step (the two of an
+    // adjoint step) stay together
+    std::vector<GenericDesc> run, longer;
+    int lds = 0, fits = i, fails = j + 1;
+    for (int t = j; fails - fits > 1; t = (fits + fails) / 2) {
+      int e = t;
+      while (e < n && e > fits && ops[e].step == ops[e - 1].step) --e;
+      longer.clear();
+      int size = 0;
+      if (e <= i + 1) {
+        fails = t;  // too short
+      } else if (e > fits && plan_run(ops, i, e, shared, longer, size)) {
+        fits = t;
+        j = e;
+        lds = size;
+        run.swap(longer);
+      } else {
+        fails = t;
       }
-      j -= std::max(1, (j - i) / 16);
     }
+    if (run.empty()) j = i;
     if (j - i >= 2) {
       flush();
       Item it;
@@ -721,7 +739,7 @@ void build_fwd_seq(ltn_plan* p, int mode) {
   descs.clear();
   std::vector<SeqOp> ops;
   auto single = [&](int what, int step) {
-    sequence_generic(ops, r.B, descs, seq);
+    sequence_generic(ops, r.B > 1, descs, seq);
     ops.clear();
     Item it;
     it.what = what;
@@ -738,7 +756,7 @@ void build_fwd_seq(ltn_plan* p, int mode) {
       ops.push_back(step_seq_op(p, s, false, mode));
     }
   }
-  sequence_generic(ops, r.B, descs, seq);
+  sequence_generic(ops, r.B > 1, descs, seq);
   int from_leaves = 0;  // leaf operands that runs read themselves
   for (const Item& it : seq)
     for (int i = 0; i < it.count && it.what == 4; ++i)
@@ -1338,16 +1356,21 @@ static void enqueue_adjoint_step(ltn_plan* p, int s, int nb) {
   const TensorPlan &ta = p->tensors[sp.a], &tb = p->tensors[sp.b], &tc = p->tensors[sp.out];
   const uint64_t cm = sp.c_mask_a;
   {
-    // small steps: one generic kernel per operand, reading the operands
-    // in place (strided) and conjugating the second one
-    if (sp.m + sp.n + sp.k <= 16) {
-      for (int which = 0; which < 2; ++which)
-        if (r.needs_grad[which ? sp.b : sp.a]) {
-          int tk = 1;
-          GenericDesc g = adj_generic_desc(p, s, which, nb, &tk);
-          launch_generic(g, tk, r.st);
-        }
-      return;
+    // small steps and products with few columns: one kernel per operand,
+    // reading the operands in place (strided) and conjugating the second one
+    bool done[2] = {!r.needs_grad[sp.a], !r.needs_grad[sp.b]};
+    for (int which = 0; which < 2; ++which) {
+      if (done[which]) continue;
+      int tk = 1;
+      const GenericDesc g = adj_generic_desc(p, s, which, nb, &tk);
+      RowsumDesc d;
+      done[which] = true;
+      if (rowsum_fits(g, d))
+        launch_rowsum(d, r.st);
+      else if (sp.m + sp.n + sp.k <= 16)
+        launch_generic(g, tk, r.st);
+      else
+        done[which] = false;
     }
     // adjoint products in the forward form: the output cotangent
     // and the other operand are permuted so that the summed bits are
@@ -1358,7 +1381,7 @@ static void enqueue_adjoint_step(ltn_plan* p, int s, int nb) {
     // positions of the m bits (in order) and the n bits of the output
     std::vector<int> mpos, npos;
     for (int j = 0; j < rc; ++j) ((cm >> j) & 1 ? mpos : npos).push_back(j);
-    if (r.needs_grad[sp.a]) {
+    if (!done[0]) {
       // dA[m][k] = sum_n dC[merge(m, n)] conj(B[n][k])
       std::vector<int32_t> pc(rc), pb(sp.k + sp.n);
       for (int i = 0; i < sp.m; ++i) pc[mpos[i]] = sp.n + i;
@@ -1370,7 +1393,7 @@ static void enqueue_adjoint_step(ltn_plan* p, int s, int nb) {
       enqueue_nt(p, X, int64_t(1) << rc, Ys, int64_t(1) << tb.rank, arena_ptr(p, ta.gcot),
                  int64_t(1) << ta.rank, sp.m, sp.n, sp.k, ((1ull << sp.m) - 1) << sp.k, nb);
     }
-    if (r.needs_grad[sp.b]) {
+    if (!done[1]) {
       // dB[n][k] = sum_m dC[merge(m, n)] conj(A[m][k])
       std::vector<int32_t> pc(rc), pa(sp.k + sp.m);
       for (int i = 0; i < sp.m; ++i) pc[mpos[i]] = i;
@@ -1422,7 +1445,7 @@ static void build_grad_seq(ltn_plan* p) {
   r.gseq_bwd.clear();
   std::vector<SeqOp> ops;
   auto single = [&](std::vector<Item>& seq, int what, int s) {
-    sequence_generic(ops, r.B, r.gseq_descs, seq);
+    sequence_generic(ops, false, r.gseq_descs, seq);
     ops.clear();
     Item it;
     it.what = what;
@@ -1435,7 +1458,7 @@ static void build_grad_seq(ltn_plan* p) {
     else
       ops.push_back(step_seq_op(p, s, true, LTN_C64));
   }
-  sequence_generic(ops, r.B, r.gseq_descs, r.gseq_fwd);
+  sequence_generic(ops, false, r.gseq_descs, r.gseq_fwd);
   ops.clear();
   const int nt = (int)p->tensors.size();
   auto range = [&](int t, bool cot) {
@@ -1446,7 +1469,16 @@ static void build_grad_seq(ltn_plan* p) {
   for (int s = (int)p->steps.size() - 1; s >= 0; --s) {
     const StepPlan& sp = p->steps[s];
     if (!r.needs_grad[sp.out]) continue;
-    if (sp.m + sp.n + sp.k > 16) {
+    bool alone = sp.m + sp.n + sp.k > 16;
+    if (!alone && sp.m + sp.n + sp.k >= kRowsumWork) {
+      alone = true;
+      for (int which = 0; which < 2; ++which) {
+        int tk;
+        RowsumDesc d;
+        if (r.needs_grad[which ? sp.b : sp.a]) alone = alone && rowsum_fits(adj_generic_desc(p, s, which, r.B, &tk), d);
+      }
+    }
+    if (alone) {
       single(r.gseq_bwd, 2, s);
       continue;
     }
@@ -1466,7 +1498,7 @@ static void build_grad_seq(ltn_plan* p) {
       ops.push_back(o);
     }
   }
-  sequence_generic(ops, r.B, r.gseq_descs, r.gseq_bwd);
+  sequence_generic(ops, false, r.gseq_descs, r.gseq_bwd);
   require(r.gseq_descs.size() <= 3 * p->steps.size(), "gradient descriptor area too small");
   if (!r.gseq_descs.empty())
     HIPCHECK(hipMemcpyAsync(r.ws + r.lay.gdesc, r.gseq_descs.data(), r.gseq_descs.size() * sizeof(GenericDesc),
