@@ -2043,9 +2043,14 @@ static PermuteDesc plan_permute(int32_t rank, const int32_t* perm, int64_t batch
   for (int y = 0; y < t; ++y) in_tile[inv[y]] = 1;     // sources of the lowest destination bits
   int nt = 0;
   for (int j = 0; j < rank; ++j) nt += in_tile[j];
-  for (int j = 0; j < rank && nt < std::min(rank, 12); ++j)
+  // filled up to 4096 elements with the next source bits, to fewer (1024 at
+  // least, so that runs stay long) while that leaves CUs without a tile: 2^19
+  // elements 8.3 -> 5.3 us, 2^16 7.4 -> 4.3
+  int fill = std::min(rank, 12);
+  while (fill > 10 && (batch << (rank - fill)) < 256) --fill;
+  for (int j = 0; j < rank && nt < fill; ++j)
     if (!in_tile[j]) {
-      in_tile[j] = 1;  // fill the tile up to 4096 elements with the next source bits
+      in_tile[j] = 1;
       ++nt;
     }
   std::vector<int> tsrc, outer;
