@@ -1,4 +1,5 @@
-// Runs of small contraction steps, one block per slice.
+// Runs of small contraction steps, one block per slice, or one per slice and group
+// of steps that do not depend on those of another.
 //
 // A step of a few hundred multiply-adds costs a launch (3-5 us, in a graph as
 // well) and its operands' way through memory; trees of random circuits begin
@@ -16,8 +17,9 @@
 //
 // What bounds it: latency (a barrier, descriptor and LDS round trip per level).
 // Measured per call, launches of independent steps -> runs: 12-qubit circuit
-// (24 steps, one slice) 65 -> 25 us, with the workspace handed in 142 -> 60 us;
-// 20-qubit circuit, 256 slices, complex64 168 -> 90 us.
+// (24 steps, one slice) 66 -> 26 us, with the workspace handed in 137 -> 63 us;
+// 20-qubit circuit, 256 slices, complex64 167 -> 77 us (88 with one group), split
+// fp16 594 us (669 with one group).
 #include <cstddef>
 
 #include "kernels.h"
@@ -132,10 +134,12 @@ __device__ __forceinline__ void small_op(const GenericDesc& d, int b, int t, int
 }
 
 template <bool ADJ>
-__global__ __launch_bounds__(kThreads) void k_small_run(const GenericDesc* __restrict__ descs, int n, int big,
+__global__ __launch_bounds__(kThreads) void k_small_run(const GenericDesc* __restrict__ all, RunGroups groups, int big,
                                                         const float2* __restrict__ leafdata,
                                                         const uint64_t* __restrict__ ids) {
   const uint64_t id = ids[blockIdx.x];
+  const GenericDesc* descs = all + groups.off[blockIdx.y];
+  const int n = groups.off[blockIdx.y + 1] - groups.off[blockIdx.y];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // inputs (operands with an address in memory) to their places: 16 lanes each,
@@ -226,16 +230,14 @@ int small_run_waves() { return kWaves; }
 
 int small_run_side() { return kSide; }
 
-void launch_small_run(const GenericDesc* d_descs, int n, bool adjoint, bool big, int lds_elems,
-                      const float2* leafdata,
-                      const uint64_t* ids, int nb, hipStream_t st) {
+void launch_small_run(const GenericDesc* d_descs, const RunGroups& groups, bool adjoint, bool big, int lds_elems,
+                      const float2* leafdata, const uint64_t* ids, int nb, hipStream_t st) {
   const size_t bytes = (size_t)lds_elems * sizeof(f2);
+  const dim3 grid((unsigned)nb, (unsigned)groups.n);
   if (adjoint)
-    hipLaunchKernelGGL(k_small_run<true>, dim3((unsigned)nb), dim3(kThreads), bytes, st, d_descs, n, big,
-                       leafdata, ids);
+    hipLaunchKernelGGL(k_small_run<true>, grid, dim3(kThreads), bytes, st, d_descs, groups, big, leafdata, ids);
   else
-    hipLaunchKernelGGL(k_small_run<false>, dim3((unsigned)nb), dim3(kThreads), bytes, st, d_descs, n, big,
-                       leafdata, ids);
+    hipLaunchKernelGGL(k_small_run<false>, grid, dim3(kThreads), bytes, st, d_descs, groups, big, leafdata, ids);
 }
 
 }  // namespace ltn

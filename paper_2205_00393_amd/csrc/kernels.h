@@ -76,6 +76,12 @@ struct ParamLeaf {
   int32_t gd;        // index of its GatherDesc (for cotangent scatter)
 };
 
+// Blocks that share a run of small steps (launch_small_run)
+constexpr int kRunGroups = 8;
+struct RunGroups {
+  int32_t n, off[kRunGroups + 1];
+};
+
 // Operand addressing of the generic contraction
 //   out[pdep(x, ox) | pdep(y, oy)] = sum_z P[pdep(x, px) | pdep(z, pz)]
 //                                        * Q[pdep(y, qy) | pdep(z, qz)]
@@ -149,13 +155,13 @@ struct RowsumDesc {
 bool rowsum_fits(const GenericDesc& g, RowsumDesc& d);  // fills d
 void launch_rowsum(const RowsumDesc& d, hipStream_t st);
 
-// A run of n small steps (device array, in level order; all forward steps or
-// all adjoint products) as one launch: one block per slice, lds_elems complex64
-// of LDS; a descriptor's nb is the place of its address tables there, in
-// 16-bit words.
+// A run of small steps (device array; all forward steps or all adjoint products)
+// as one launch: per slice one block for each group, whose steps are descs[off[g]
+// .. off[g + 1]) in level order; lds_elems complex64 of LDS; a descriptor's nb is
+// the place of its address tables there, in 16-bit words.
 int small_run_waves();
 int small_run_side();  // inputs above this size are `big`
-void launch_small_run(const GenericDesc* d_descs, int n, bool adjoint, bool big, int lds_elems,
+void launch_small_run(const GenericDesc* d_descs, const RunGroups& groups, bool adjoint, bool big, int lds_elems,
                       const float2* leafdata, const uint64_t* ids, int nb, hipStream_t st);
 
 // C[merge(m, n)] = sum_k A[m 2^k + k] B[n 2^k + k] on FP32 MFMA; the output

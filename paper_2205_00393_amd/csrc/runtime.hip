@@ -78,6 +78,7 @@ struct ltn_plan_impl {
     int what = 0;
     int step = -1, off = 0, count = 0, tk = 1, lds = 0;
     uint64_t max_outs = 0;
+    RunGroups groups{};
   };
   // forward kept in the gradient arena by the last ltn_execute (plan bound
   // for gradients, complex64, one batch) and its slice ids: ltn_execute_grad
@@ -434,7 +435,7 @@ void enqueue_group(ltn_plan* p, int g, int nb, int mode) {
 // A launch of generic contractions (what 1 or 4) from descriptors in memory.
 void enqueue_generic(ltn_plan* p, const GenericDesc* dd, const ltn_plan_impl::GradItem& it, int nb) {
   if (it.what == 4)
-    launch_small_run(dd + it.off, it.count, it.step == 1, it.tk == 2, it.lds,
+    launch_small_run(dd + it.off, it.groups, it.step == 1, it.tk == 2, it.lds,
                      reinterpret_cast<const float2*>(p->rt->ws + p->rt->lay.leafdata),
                      reinterpret_cast<const uint64_t*>(p->rt->ws + p->rt->lay.ids), nb, p->rt->st);
   else
@@ -512,12 +513,48 @@ struct SeqOp {
 constexpr int kRowsumWork = 13;
 constexpr int kRunWork = 15, kWaveWork = 11, kRunSteps = 96, kRunLds = 8192;
 
-// Plan ops[i .. j) as one run: levels by dependence, places in LDS by first fit
-// over the levels a tensor is needed in, waves. False when LDS does not hold it
-// or when a block could write memory that another block of the run still reads
-// (`shared`: the arena reuses memory across tensors, whose slices then overlap;
-// not with one slice, where the one block has read its inputs before it writes).
-bool plan_run(const std::vector<SeqOp>& ops, int i, int j, bool shared, std::vector<GenericDesc>& out, int& lds) {
+// Which step of ops[i .. j) produces an operand (-1: none), and which outputs are
+// needed in memory.
+struct RunLinks {
+  std::vector<std::array<int, 2>> from;
+  std::vector<char> ext;
+  RunLinks(const std::vector<SeqOp>& ops, int i, int j) : from(j - i, {-1, -1}), ext(j - i, 1) {
+    std::unordered_map<int, int> made, step_of;
+    for (int k = 0; k < j - i; ++k) {
+      const SeqOp& o = ops[i + k];
+      for (int q = 0; q < 2; ++q)
+        if (auto it = made.find(o.in[q]); it != made.end()) from[k][q] = it->second;
+      made[o.out] = k;
+      step_of[o.step] = k;
+    }
+    for (int k = 0; k < j - i; ++k)
+      if (auto it = step_of.find(ops[i + k].consumer); !ops[i + k].keep && it != step_of.end() && it->second > k)
+        ext[k] = 0;
+  }
+};
+
+// Whether a block of the run ops[i .. j) could write memory that another block
+// of it still reads or writes: the arena reuses memory across tensors, whose
+// slices then overlap.
+bool run_clashes(const std::vector<SeqOp>& ops, int i, int j, const RunLinks& l) {
+  for (int k = 0; k < j - i; ++k) {
+    if (!l.ext[k]) continue;
+    const auto& w = ops[i + k].rout;
+    for (int m = 0; m < j - i; ++m) {
+      if (m != k && l.ext[m] && w.meets(ops[i + m].rout)) return true;
+      for (int q = 0; q < 2; ++q)
+        if (l.from[m][q] < 0 && !ops[i + m].leaf[q] && w.meets(ops[i + m].rin[q])) return true;
+    }
+  }
+  return false;
+}
+
+// Plan ops as the run of one block: levels by dependence, places in LDS by first
+// fit over the levels a tensor is needed in, waves. False when LDS does not hold
+// it.
+bool plan_run(const std::vector<SeqOp>& ops, std::vector<GenericDesc>& out, int& lds) {
+  constexpr int i = 0;
+  const int j = (int)ops.size();
   const int n = j - i;
   struct Place {
     int off, size, from, to;
@@ -538,32 +575,15 @@ bool plan_run(const std::vector<SeqOp>& ops, int i, int j, bool shared, std::vec
     lds = std::max(lds, off + size);
     return off;
   };
+  const RunLinks links(ops, i, j);
+  const auto& from = links.from;
+  const auto& ext = links.ext;
   std::vector<int> level(n, 1), last(n, 0);
-  std::vector<std::array<int, 2>> from(n, {-1, -1});  // producers inside the run
-  std::vector<char> ext(n, 1);
-  std::unordered_map<int, int> made, step_of;
   for (int k = 0; k < n; ++k) {
-    const SeqOp& o = ops[i + k];
     for (int q = 0; q < 2; ++q)
-      if (auto it = made.find(o.in[q]); it != made.end()) {
-        from[k][q] = it->second;
-        level[k] = std::max(level[k], level[it->second] + 1);
-      }
+      if (from[k][q] >= 0) level[k] = std::max(level[k], level[from[k][q]] + 1);
     for (int q = 0; q < 2; ++q)
       if (from[k][q] >= 0) last[from[k][q]] = std::max(last[from[k][q]], level[k]);
-    made[o.out] = k;
-    step_of[o.step] = k;
-  }
-  for (int k = 0; k < n; ++k)
-    if (auto it = step_of.find(ops[i + k].consumer); !ops[i + k].keep && it != step_of.end() && it->second > k) ext[k] = 0;
-  for (int k = 0; k < n && shared; ++k) {
-    if (!ext[k]) continue;
-    const auto& w = ops[i + k].rout;
-    for (int m = 0; m < n; ++m) {
-      if (m != k && ext[m] && w.meets(ops[i + m].rout)) return false;
-      for (int q = 0; q < 2; ++q)
-        if (from[m][q] < 0 && !ops[i + m].leaf[q] && w.meets(ops[i + m].rin[q])) return false;
-    }
   }
   lds = 0;
   std::vector<std::array<int, 3>> at(n, {-1, -1, -1});
@@ -624,11 +644,63 @@ bool plan_run(const std::vector<SeqOp>& ops, int i, int j, bool shared, std::vec
   return true;
 }
 
+// Plan ops[i .. j) as one run of nb slices: steps that depend on each other stay
+// together, and what does not is spread over up to eight blocks per slice while
+// that gives no more than two blocks a CU (a run is a chain of latencies: 64
+// slices of a 20-qubit circuit's first 96 steps on one block each 42 us). `reused`:
+// the arena's memory serves several tensors; with one block, which has read its
+// inputs before it writes, that does not matter.
+bool plan_groups(const std::vector<SeqOp>& ops, int i, int j, int nb, bool reused, std::vector<GenericDesc>& out,
+                 RunGroups& groups, int& lds) {
+  const int n = j - i;
+  const RunLinks links(ops, i, j);
+  // trees of the run: the last step of a tree stands for it
+  std::vector<int> root(n);
+  for (int k = 0; k < n; ++k) root[k] = k;
+  auto find = [&](int k) {
+    while (root[k] != k) k = root[k] = root[root[k]];
+    return k;
+  };
+  for (int k = 0; k < n; ++k)
+    for (int q = 0; q < 2; ++q)
+      if (links.from[k][q] >= 0) root[find(links.from[k][q])] = find(k);
+  std::vector<std::pair<int, int>> trees;  // cost, root
+  std::vector<int> cost(n, 0);
+  for (int k = 0; k < n; ++k) cost[find(k)] += 2 + (1 << std::max(0, ops[i + k].work() - 9));
+  for (int k = 0; k < n; ++k)
+    if (root[k] == k) trees.push_back({cost[k], k});
+  int G = std::max(1, std::min({(int)trees.size(), kRunGroups, 512 / nb}));
+  if (reused && (nb > 1 || G > 1) && run_clashes(ops, i, j, links)) {
+    if (nb > 1) return false;
+    G = 1;
+  }
+  std::sort(trees.begin(), trees.end(), [](auto& a, auto& b) { return a.first > b.first; });
+  std::vector<int> load(G, 0), group(n, 0);
+  for (auto& t : trees) {
+    const int g = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+    load[g] += t.first;
+    group[t.second] = g;
+  }
+  groups = RunGroups{};
+  groups.n = G;
+  lds = 0;
+  for (int g = 0; g < G; ++g) {
+    std::vector<SeqOp> mine;
+    for (int k = 0; k < n; ++k)
+      if (group[find(k)] == g) mine.push_back(ops[i + k]);
+    int size = 0;
+    if (!plan_run(mine, out, size)) return false;
+    lds = std::max(lds, size);
+    groups.off[g + 1] = (int)out.size();
+  }
+  return true;
+}
+
 // Launches of consecutive generic contractions: runs of small steps where two
 // or more fit one, else launches of independent steps (a step joins the launch
 // unless it reads, or writes over, what a member writes, or writes over what a
 // member reads).
-void sequence_generic(const std::vector<SeqOp>& ops, bool shared, std::vector<GenericDesc>& descs,
+void sequence_generic(const std::vector<SeqOp>& ops, int nb, bool reused, std::vector<GenericDesc>& descs,
                       std::vector<ltn_plan_impl::GradItem>& seq) {
   using Item = ltn_plan_impl::GradItem;
   std::vector<const SeqOp*> group;
@@ -656,6 +728,7 @@ void sequence_generic(const std::vector<SeqOp>& ops, bool shared, std::vector<Ge
     // adjoint step) stay together
     std::vector<GenericDesc> run, longer;
     int lds = 0, fits = i, fails = j + 1;
+    RunGroups groups{}, more;
     for (int t = j; fails - fits > 1; t = (fits + fails) / 2) {
       int e = t;
       while (e < n && e > fits && ops[e].step == ops[e - 1].step) --e;
@@ -663,10 +736,11 @@ void sequence_generic(const std::vector<SeqOp>& ops, bool shared, std::vector<Ge
       int size = 0;
       if (e <= i + 1) {
         fails = t;  // too short
-      } else if (e > fits && plan_run(ops, i, e, shared, longer, size)) {
+      } else if (e > fits && plan_groups(ops, i, e, nb, reused, longer, more, size)) {
         fits = t;
         j = e;
         lds = size;
+        groups = more;
         run.swap(longer);
       } else {
         fails = t;
@@ -680,6 +754,7 @@ void sequence_generic(const std::vector<SeqOp>& ops, bool shared, std::vector<Ge
       it.off = (int)descs.size();
       it.count = j - i;
       it.lds = lds;
+      it.groups = groups;
       it.step = run[0].conjQ() ? 1 : 0;
       for (auto& g : run) {
         const int p = g.P ? 1 << (g.xb() + g.zb()) : 0, q = g.Q ? 1 << (g.yb() + g.zb()) : 0;
@@ -739,7 +814,7 @@ void build_fwd_seq(ltn_plan* p, int mode) {
   descs.clear();
   std::vector<SeqOp> ops;
   auto single = [&](int what, int step) {
-    sequence_generic(ops, r.B > 1, descs, seq);
+    sequence_generic(ops, r.B, true, descs, seq);
     ops.clear();
     Item it;
     it.what = what;
@@ -756,7 +831,7 @@ void build_fwd_seq(ltn_plan* p, int mode) {
       ops.push_back(step_seq_op(p, s, false, mode));
     }
   }
-  sequence_generic(ops, r.B > 1, descs, seq);
+  sequence_generic(ops, r.B, true, descs, seq);
   int from_leaves = 0;  // leaf operands that runs read themselves
   for (const Item& it : seq)
     for (int i = 0; i < it.count && it.what == 4; ++i)
@@ -1445,7 +1520,7 @@ static void build_grad_seq(ltn_plan* p) {
   r.gseq_bwd.clear();
   std::vector<SeqOp> ops;
   auto single = [&](std::vector<Item>& seq, int what, int s) {
-    sequence_generic(ops, false, r.gseq_descs, seq);
+    sequence_generic(ops, r.B, false, r.gseq_descs, seq);
     ops.clear();
     Item it;
     it.what = what;
@@ -1458,7 +1533,7 @@ static void build_grad_seq(ltn_plan* p) {
     else
       ops.push_back(step_seq_op(p, s, true, LTN_C64));
   }
-  sequence_generic(ops, false, r.gseq_descs, r.gseq_fwd);
+  sequence_generic(ops, r.B, false, r.gseq_descs, r.gseq_fwd);
   ops.clear();
   const int nt = (int)p->tensors.size();
   auto range = [&](int t, bool cot) {
@@ -1498,7 +1573,7 @@ static void build_grad_seq(ltn_plan* p) {
       ops.push_back(o);
     }
   }
-  sequence_generic(ops, false, r.gseq_descs, r.gseq_bwd);
+  sequence_generic(ops, r.B, false, r.gseq_descs, r.gseq_bwd);
   require(r.gseq_descs.size() <= 3 * p->steps.size(), "gradient descriptor area too small");
   if (!r.gseq_descs.empty())
     HIPCHECK(hipMemcpyAsync(r.ws + r.lay.gdesc, r.gseq_descs.data(), r.gseq_descs.size() * sizeof(GenericDesc),
