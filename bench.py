@@ -62,13 +62,16 @@ def counter_traffic(workload, mode, kern):
 def step_roofline(kind, tile, m, k, n, batch):
     """Algorithmic flops, executed matrix flops, algorithmic bytes of one
     matrix-core step (kind 1/5 complex64 tiles, kind 2 split tiles, kind 6
-    complex64 tiles on three bf16 parts) over a batch, and whether it is GEMM-bound: executed flops per algorithmic byte
-    at or above the ridge of its matrix peak and the 8 TB/s HBM peak.
+    complex64 tiles on parts) over a batch, and whether it is GEMM-bound:
+    executed flops per algorithmic byte at or above the ridge of its matrix
+    peak and the 8 TB/s HBM peak.
     Executed flops per complex MAC: 8 on direct complex64 tiles, 6 on the
     three-product ones (names with _3m_), 24 on split tiles, 36 on three-part
-    tiles (three real products of six products of parts)."""
+    bf16 tiles (three real products of six products of parts), 18 on two-part
+    fp16 tiles (names with parts2_; three products of parts)."""
     f = 8.0 * (1 << (m + k + n)) * batch
-    fx = f * (3.0 if kind == 2 else 4.5 if kind == 6 else (0.75 if "_3m_" in tile else 1.0))
+    fx = f * (3.0 if kind == 2 else (2.25 if "parts2_" in tile else 4.5) if kind == 6
+              else (0.75 if "_3m_" in tile else 1.0))
     by = 8.0 * ((1 << (m + k)) + (1 << (n + k)) + (1 << (m + n))) * batch
     peak = PEAK_F16_MFMA_TFLOPS if kind in (2, 6) else PEAK_FP32_MFMA_TFLOPS
     return f, fx, by, fx / by >= peak / PEAK_HBM_GBS * 1e3
@@ -346,8 +349,8 @@ def roofline_of(workload, mode, r):
     the complex64 GEMM on FP32 matrix cores, whose achieved rate counts 8
     algorithmic flops per complex MAC (its three-product tiles execute 6, so
     the rate can pass the FP32 matrix peak by up to 4/3), or the split and
-    the three-part GEMM, whose achieved rate is what the FP16/BF16 matrix
-    cores execute (24 and 36 flops per complex MAC). `executed` and
+    the parts GEMM, whose achieved rate is what the FP16/BF16 matrix cores
+    execute (24, and 36 or 18 flops per complex MAC). `executed` and
     `executed_frac` give what the matrix cores ran."""
     kernel = max(("k_cgemm_c64", "k_cgemm_split", "k_cgemm_parts"), key=lambda n: r["kernels"][n]["ms_per_batch"])
     e = r["kernels"][kernel]
@@ -362,7 +365,8 @@ def roofline_of(workload, mode, r):
             "executed_flops_per_complex_mac":
             {"k_cgemm_c64": "6 on c64_3m/splitk_3m tiles, 8 on direct complex64 tiles",
              "k_cgemm_split": "24 (three fp16/bf16 products of the 2x2 real form)",
-             "k_cgemm_parts": "36 (six bf16 products of each of three real products)"}[kernel],
+             "k_cgemm_parts": "36 (six bf16 products of each of three real products), 18 on parts2 tiles "
+                              "(three fp16 products)"}[kernel],
             "gemm_bound_steps": {"launches": e["gemm_bound"]["launches"],
                                  "share_of_kernel_time": round(e["gemm_bound"]["ms_per_batch"] / e["ms_per_batch"], 4)
                                  if e["ms_per_batch"] > 0 else 0.0,
