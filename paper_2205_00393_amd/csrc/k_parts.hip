@@ -103,7 +103,14 @@ __device__ __forceinline__ float fp16_up(uint32_t maxbits) {
 
 // SPLITK: block w takes chunk w / (tiles * nb) of the sum for tile w % (tiles *
 // nb) and writes its FP32 partial of C to part, as k_cgemm_c64's split-K form.
-template <int BM, int BN, int PARTS, bool SPLITK>
+// INPLACE: rows and sum of either operand at any address bits, either operand
+// conjugated (adjoint products on the operands of the forward step). The lanes of
+// an operand run along its sum as above where that has the lowest address bit,
+// else along its rows, whose elements are then neighbours.
+// 256 slices, permutations of both operands and the plain tile -> in place: (11 rows,
+// sum 9, 7 columns) 1.93 -> 1.29 ms, (9,11,7) 2.05 -> 1.47, (10,6,10) 0.91 -> 1.10 and
+// (6,10,10) 1.56 -> 0.82.
+template <int BM, int BN, int PARTS, bool SPLITK, bool INPLACE>
 __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   constexpr int T = 256, KT = 16, NWM = 2, NWN = 2;
   constexpr int WM = BM / NWM, WN = BN / NWN, TM = WM / 32, TN = WN / 32;
@@ -121,8 +128,8 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   tile_of(w, M / BM, N / BN, d.nb, b, bm, bn);
   const int64_t KL = SPLITK ? (int64_t(1) << d.kc_bits) : K;
   const int nt = (int)(KL / KT);
-  const float2* A = d.A + b * d.sA + bm * BM * K + chunk * KL;
-  const float2* B = d.B + b * d.sB + bn * BN * K + chunk * KL;
+  const float2* A = d.A + b * d.sA + (INPLACE ? (int64_t)pdep64((uint64_t)(bm * BM), d.arow) : bm * BM * K + chunk * KL);
+  const float2* B = d.B + b * d.sB + (INPLACE ? (int64_t)pdep64((uint64_t)(bn * BN), d.brow) : bn * BN * K + chunk * KL);
   const float ua = PARTS == 3 ? kUp : fp16_up(d.scale_a[b]), ub = PARTS == 3 ? kUp : fp16_up(d.scale_b[b]);
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -135,19 +142,62 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   const float4* src[R];
   float up[R];
   int dst[R];
+  // INPLACE: round 0 is A's, round 1 B's; the weights of the lowest four sum bits
+  // and the tile's offset in the sum
+  static_assert(!INPLACE || (2 * BM == T && R == 2 && PARTS == 3), "one round of threads per operand");
+  int64_t weight[2][4];
+  uint64_t at[2] = {0, 0}, step[2];
+  if constexpr (INPLACE) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const uint64_t sum = r ? d.bsum : d.asum;
+      step[r] = pdep64(KT, sum);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) weight[r][j] = (int64_t)pdep64(1ull << j, sum);
+    }
+  }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int c = tid + T * r, row = c >> 1, g = c & 1;
-    src[r] = reinterpret_cast<const float4*>(row < BM ? A + row * K : B + (row - BM) * K) + g;
+    const int c = tid + T * r;
+    int row = c >> 1, g = c & 1;
+    if constexpr (INPLACE) {
+      constexpr int rows[2] = {BM, BN};
+      if (!((r ? d.bsum : d.asum) & 1)) {
+        g = (tid / rows[r]) & 1;  // threads past the operand have no group
+        row = (tid & (rows[r] - 1)) + (r ? BM : 0);
+      }
+      src[r] = reinterpret_cast<const float4*>((r ? B + pdep64((uint64_t)(row - BM) & (BN - 1), d.brow)
+                                                  : A + pdep64((uint64_t)row, d.arow)) + g * weight[r][1]);
+    } else {
+      src[r] = reinterpret_cast<const float4*>(row < BM ? A + row * K : B + (row - BM) * K) + g;
+    }
     up[r] = PARTS == 3 ? kUp : (row < BM ? ua : ub);
     dst[r] = 2 * row + (g ^ ((row >> 3) & 1));
   }
   // one k-tile of group r, and on to the next tile (`more`: there is one)
   auto load = [&](int r, float4 (&v)[4], bool more) {
     if (!has(r)) return;
+    if constexpr (INPLACE) {
+      const float2* p = reinterpret_cast<const float2*>(src[r]) + at[r];
+      if (weight[r][0] == 1) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = src[r][2 * q];
-    src[r] += more ? KT / 2 : 0;
+        for (int q = 0; q < 4; ++q)
+          v[q] = *reinterpret_cast<const float4*>(p + ((q & 1) * weight[r][2] + (q >> 1) * weight[r][3]));
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float2* s = p + ((q & 1) * weight[r][2] + (q >> 1) * weight[r][3]);
+          const float2 x = s[0], y = s[weight[r][0]];
+          v[q] = make_float4(x.x, x.y, y.x, y.y);
+        }
+      }
+      const uint64_t sum = r ? d.bsum : d.asum;
+      if (more) at[r] = ((at[r] | ~sum) + step[r]) & sum;
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = src[r][2 * q];
+      src[r] += more ? KT / 2 : 0;
+    }
   };
   auto stash = [&](int r, const float4 (&v)[4]) {
     if (!has(r)) return;
@@ -158,6 +208,11 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
       im[2 * q] = v[q].y;
       re[2 * q + 1] = v[q].z;
       im[2 * q + 1] = v[q].w;
+    }
+    if constexpr (INPLACE) {
+      const float sign = (r ? d.conj_b : d.conj_a) ? -1.f : 1.f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) im[q] *= sign;
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) su[q] = re[q] + im[q];
@@ -301,12 +356,17 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
     for (int e = 0; e < 16 * TM * TN; ++e) {
       const int64_t row = wm * WM + 32 * (e / (16 * TN)) + 8 * ((e >> 2) & 3) + 4 * h + (e & 3);
       const int64_t col = wn * WN + 32 * ((e >> 4) % TN) + i;
-      const float2 *a = A + row * K, *q = B + col * K;
+      const float2* a = A + (INPLACE ? (int64_t)pdep64((uint64_t)row, d.arow) : row * K);
+      const float2* q = B + (INPLACE ? (int64_t)pdep64((uint64_t)col, d.brow) : col * K);
       float p1 = 0.f, p2 = 0.f, p3 = 0.f;
       for (int64_t k = 0; k < KL; ++k) {
-        p1 = fmaf(a[k].x, q[k].x, p1);
-        p2 = fmaf(a[k].y, q[k].y, p2);
-        p3 = fmaf(a[k].x + a[k].y, q[k].x + q[k].y, p3);
+        float2 u = a[INPLACE ? (int64_t)pdep64((uint64_t)k, d.asum) : k];
+        float2 v = q[INPLACE ? (int64_t)pdep64((uint64_t)k, d.bsum) : k];
+        if (INPLACE && d.conj_a) u.y = -u.y;
+        if (INPLACE && d.conj_b) v.y = -v.y;
+        p1 = fmaf(u.x, v.x, p1);
+        p2 = fmaf(u.y, v.y, p2);
+        p3 = fmaf(u.x + u.y, v.x + v.y, p3);
       }
       const float re = p1 - p2, im = p3 - p1 - p2;
       vmax = fmaxf(vmax, fmaxf(fabsf(re), fabsf(im)));
@@ -316,11 +376,11 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   if (!SPLITK && d.scale_c) block_raise_max(d.scale_c + b, vmax, reinterpret_cast<float*>(S));
 }
 
-template <int BM, int BN, int PARTS, bool SPLITK>
+template <int BM, int BN, int PARTS, bool SPLITK, bool INPLACE = false>
 void run_parts(const GemmDesc& d, hipStream_t st) {
   const int64_t chunks = SPLITK ? int64_t(1) << (d.k - d.kc_bits) : 1;
   const int64_t blocks = ((int64_t(1) << d.m) / BM) * ((int64_t(1) << d.n) / BN) * d.nb * chunks;
-  hipLaunchKernelGGL((k_cgemm_parts<BM, BN, PARTS, SPLITK>), dim3((unsigned)blocks), dim3(256), 0, st, d);
+  hipLaunchKernelGGL((k_cgemm_parts<BM, BN, PARTS, SPLITK, INPLACE>), dim3((unsigned)blocks), dim3(256), 0, st, d);
 }
 
 struct PartsCfg {
@@ -376,6 +436,8 @@ const char* parts_config_name(int cfg, int mode) {
 // where a long sum leaves at most one 64 x 64 split tile per CU ((13,14,7) 0.59
 // against 1.16 ms, (14,13,6) 0.40 against 0.81; with two per CU, (12,13,9):
 // 0.59 against 0.51, and with a shorter sum, (10,12,10): 0.171 against 0.148).
+bool parts_config_in_place(int cfg) { return cfg == 0 || cfg == 1; }
+
 int parts_config_default(int m, int k, int n, int64_t nb, int mode) {
   if (m < 7 || n < 6 || m + n > 40) return -1;
   const bool wide = n >= 7, f16 = mode == LTN_SPLIT_F16;
@@ -400,6 +462,13 @@ int parts_config_default(int m, int k, int n, int64_t nb, int mode) {
 void launch_cgemm_parts(const GemmDesc& d0, hipStream_t st) {
   GemmDesc d = d0;
   if (parts_config_splitk(d.cfg)) d.kc_bits = d.k - splitk_chunk_bits(d.m, d.k, d.n);
+  if (d.asum) {
+    if (d.cfg == 0)
+      run_parts<128, 128, 3, false, true>(d, st);
+    else
+      run_parts<128, 64, 3, false, true>(d, st);
+    return;
+  }
   switch (d.cfg) {
     case 0: run_parts<128, 128, 3, false>(d, st); break;
     case 1: run_parts<128, 64, 3, false>(d, st); break;

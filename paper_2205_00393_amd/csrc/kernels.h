@@ -184,6 +184,10 @@ struct GemmDesc {
   uint32_t* bound_c;         //   and is stored here per slice for the consumer
   float2* part;              // split-K: [nb][chunks][2^(m+n)] FP32 partial sums
   int32_t kc_bits;           // split-K: log2 of the sum length of one chunk
+  // full complex64 parts tiles, if set: the address bits of A's and B's rows and
+  // sum (else rows of 2^k elements), and which operand is conjugated
+  uint64_t arow, asum, brow, bsum;
+  int32_t conj_a, conj_b;
 };
 // Tile plan of a bit permutation (built on the host by ltn_permute).
 struct PermuteDesc {
@@ -285,6 +289,7 @@ bool parts_config_fits(int cfg, int m, int k, int n, int mode);
 bool parts_config_splitk(int cfg);
 const char* parts_config_name(int cfg, int mode);
 // Untuned rule: the configuration to take for nb slices, or -1.
+bool parts_config_in_place(int cfg);  // takes arow .. conj_b
 int parts_config_default(int m, int k, int n, int64_t nb, int mode);
 void launch_cgemm_parts(const GemmDesc& d, hipStream_t st);
 // complex64 tensor X (2^rank per slice, rank >= 2) -> its split-layout
