@@ -17,7 +17,7 @@
 //
 // What bounds it: latency (a barrier, descriptor and LDS round trip per level).
 // Measured per call, launches of independent steps -> runs: 12-qubit circuit
-// (24 steps, one slice) 66 -> 26 us, with the workspace handed in 137 -> 63 us;
+// (24 steps, one slice) 66 -> 26 us, in the library's scratch 137 -> 64 us;
 // 20-qubit circuit, 256 slices, complex64 167 -> 77 us (88 with one group), split
 // fp16 594 us (669 with one group).
 #include <cstddef>

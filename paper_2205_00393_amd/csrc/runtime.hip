@@ -110,6 +110,8 @@ Layout layout(const ltn_plan* p, int B, int grad) {
   o = al(o + (size_t)p->leaf_elems * 8);
   l.gd_fwd = o;
   o = al(o + p->leaves.size() * sizeof(GatherDesc));
+  l.fdesc = o;  // forward runs: one descriptor per step and mode
+  o = al(o + 3 * std::max<size_t>(1, p->steps.size()) * sizeof(GenericDesc));
   l.gd_grad = o;
   o = al(o + (grad ? p->leaves.size() * sizeof(GatherDesc) : 0));
   l.gd_gcot = o;
@@ -159,8 +161,6 @@ Layout layout(const ltn_plan* p, int B, int grad) {
   o = al(o + (size_t)B * (size_t)kp * 8);
   l.gdesc = o;  // gradient runs: at most one descriptor per step forward, two backward
   if (grad) o = al(o + 3 * p->steps.size() * sizeof(GenericDesc));
-  l.fdesc = o;  // forward runs: one descriptor per step and mode
-  o = al(o + 3 * std::max<size_t>(1, p->steps.size()) * sizeof(GenericDesc));
   l.total = o;
   return l;
 }
@@ -805,7 +805,7 @@ SeqOp step_seq_op(ltn_plan* p, int s, bool gradarena, int mode) {
 // Forward launch sequence of a mode. Fused sub-paths keep their launch at
 // their last step. Descriptors (for the bound batch size) are copied to the
 // workspace here, outside any capture.
-void build_fwd_seq(ltn_plan* p, int mode) {
+void build_fwd_seq(ltn_plan* p, int mode, bool upload = true) {
   auto& r = *p->rt;
   using Item = ltn_plan_impl::GradItem;
   auto& seq = r.fseq[mode];
@@ -838,7 +838,7 @@ void build_fwd_seq(ltn_plan* p, int mode) {
       from_leaves += descs[it.off + i].leafP() + descs[it.off + i].leafQ();
   r.fseq_gather[mode] = from_leaves < (int)p->leaves.size();
   require(descs.size() <= p->steps.size(), "forward descriptor area too small");
-  if (!descs.empty()) {
+  if (!descs.empty() && upload) {
     char* dst = r.ws + r.lay.fdesc + (size_t)mode * p->steps.size() * sizeof(GenericDesc);
     HIPCHECK(hipMemcpyAsync(dst, descs.data(), descs.size() * sizeof(GenericDesc), hipMemcpyHostToDevice, r.st));
     // the host array may be rebuilt by a later call: let the copy finish
@@ -969,9 +969,10 @@ int fit_batch(const ltn_plan* p, size_t bytes, int grad, int cap) {
 
 // Fill a device-side state for the workspace d_ws (batch B): gather
 // descriptors, default kernel choices, and the uploads of leaf data and
-// descriptors, synchronised on `st` before returning.
+// descriptors, synchronised on `st` before returning. With `only`, a state for
+// one mode whose caller uploads leaf data and descriptors.
 void bind_state(ltn_plan* p, ltn_plan_impl* r, char* d_ws, size_t bytes, int grad, hipStream_t st,
-                int B) {
+                int B, int only = -1) {
   r->st = st;
   r->ws = d_ws;
   r->bytes = bytes;
@@ -1015,6 +1016,10 @@ void bind_state(ltn_plan* p, ltn_plan_impl* r, char* d_ws, size_t bytes, int gra
   for (int mode = 0; mode < 3; ++mode)
     for (auto& sp : p->steps) {
       ltn_plan_impl::Choice ch;
+      if (only >= 0 && mode != only) {
+        r->choice[mode].push_back(ch);
+        continue;
+      }
       ch.tk = default_tk(sp.k, (1ull << (sp.m + sp.n)) * (uint64_t)B);
       if (sp.kernel == LTN_K_MFMA) {
         // MFMA columns follow the output's lowest bits when possible.
@@ -1096,6 +1101,7 @@ void bind_state(ltn_plan* p, ltn_plan_impl* r, char* d_ws, size_t bytes, int gra
       r->needs_grad[v] = r->needs_grad[sp.left] || r->needs_grad[sp.right];
     }
   }
+  if (only >= 0) return;
   // uploads (host vectors live in the plan / impl; synchronised below)
   HIPCHECK(hipMemcpyAsync(r->ws + r->lay.leafdata, p->leaf_data.data(), (size_t)p->leaf_elems * 8,
                           hipMemcpyHostToDevice, r->st));
@@ -1239,8 +1245,18 @@ extern "C" ltn_status ltn_execute_scratch(ltn_plan* p, const uint64_t* ids, uint
     ltn_plan_impl* bound = p->rt;
     p->rt = &tmp;
     try {
-      bind_state(p, &tmp, ws, LTN_SCRATCH_BYTES, 0, reinterpret_cast<hipStream_t>(stream), B);
-      build_fwd_seq(p, mode);
+      bind_state(p, &tmp, ws, LTN_SCRATCH_BYTES, 0, reinterpret_cast<hipStream_t>(stream), B, mode);
+      build_fwd_seq(p, mode, false);
+      // leaf data and descriptors, which lie in a row, in one copy (three with
+      // two waits took 20 of a 12-qubit amplitude's 64 us)
+      const auto& descs = tmp.fseq_descs[mode];
+      const size_t fdesc = tmp.lay.fdesc + (size_t)mode * p->steps.size() * sizeof(GenericDesc);
+      std::vector<char> host(fdesc + descs.size() * sizeof(GenericDesc));
+      std::memcpy(host.data() + tmp.lay.leafdata, p->leaf_data.data(), (size_t)p->leaf_elems * 8);
+      std::memcpy(host.data() + tmp.lay.gd_fwd, tmp.gd_fwd.data(), tmp.gd_fwd.size() * sizeof(GatherDesc));
+      std::memcpy(host.data() + fdesc, descs.data(), descs.size() * sizeof(GenericDesc));
+      HIPCHECK(hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice, tmp.st));
+      HIPCHECK(hipStreamSynchronize(tmp.st));
       for (uint64_t off = 0; off < n; off += (uint64_t)B) {
         const int nb = (int)std::min<uint64_t>((uint64_t)B, n - off);
         set_ids(p, ids + off, 0, nb, false);
