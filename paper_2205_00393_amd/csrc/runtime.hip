@@ -903,9 +903,10 @@ void launch_captured(ltn_plan* p, hipGraphExec_t& exec, hipGraph_t& src, F&& enq
 void run_batch(ltn_plan* p, int nb, int mode, double* out) {
   auto& r = *p->rt;
   if (!r.fseq_valid[mode]) build_fwd_seq(p, mode);
-  // a graph pays from a handful of launches (one launch: 3 us directly, 10 us
-  // as a graph)
-  if (nb == r.B && r.fseq[mode].size() > 3) {
+  // A graph pays from about ten launches: one costs 3 us directly and 10 us as a
+  // graph, calls of six to eight in a row 60 -> 54 and 77 -> 73 us directly, and at
+  // 16 a call alone takes longer (95 -> 99 us).
+  if (nb == r.B && r.fseq[mode].size() > 8) {
     launch_captured(p, r.graph[mode], r.graph_src[mode], [&] { enqueue_forward(p, nb, false, mode); });
   } else {
     enqueue_forward(p, nb, false, mode);
