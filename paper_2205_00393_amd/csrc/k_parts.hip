@@ -92,14 +92,16 @@ __device__ __forceinline__ floatx16 mfma_part(u32x4 a, u32x4 b, floatx16 c) {
                                                   __builtin_bit_cast(SplitType<false>::V8, b), c, 0, 0, 0);
 }
 
-// Two fp16 parts: the operand's largest |Re|, |Im| goes to [2^13, 2^14), so that
-// Re + Im stays below 2^15
-__device__ __forceinline__ float fp16_up(uint32_t maxbits) {
+// Two fp16 parts: log2 of the scale that takes the operand's largest |Re|, |Im| to
+// [2^13, 2^14), so that Re + Im stays below 2^15. At most 2^127: there fp16's
+// smallest number stands for 2^-151, so smaller operands lose nothing.
+__device__ __forceinline__ int fp16_up(uint32_t maxbits) {
   const int e = (int)((maxbits >> 23) & 0xff);
-  if (e == 0 || e == 0xff) return 1.f;
-  const int se = 267 - e;
-  return __uint_as_float((uint32_t)(se > 254 ? 254 : se) << 23);
+  if (e == 0 || e == 0xff) return 0;
+  return e < 13 ? 127 : 140 - e;
 }
+
+__device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
 
 // SPLITK: block w takes chunk w / (tiles * nb) of the sum for tile w % (tiles *
 // nb) and writes its FP32 partial of C to part, as k_cgemm_c64's split-K form.
@@ -130,7 +132,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   const int nt = (int)(KL / KT);
   const float2* A = d.A + b * d.sA + (INPLACE ? (int64_t)pdep64((uint64_t)(bm * BM), d.arow) : bm * BM * K + chunk * KL);
   const float2* B = d.B + b * d.sB + (INPLACE ? (int64_t)pdep64((uint64_t)(bn * BN), d.brow) : bn * BN * K + chunk * KL);
-  const float ua = PARTS == 3 ? kUp : fp16_up(d.scale_a[b]), ub = PARTS == 3 ? kUp : fp16_up(d.scale_b[b]);
+  const int ea = PARTS == 3 ? 0 : fp16_up(d.scale_a[b]), eb = PARTS == 3 ? 0 : fp16_up(d.scale_b[b]);
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tid = threadIdx.x;
@@ -171,7 +173,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
     } else {
       src[r] = reinterpret_cast<const float4*>(row < BM ? A + row * K : B + (row - BM) * K) + g;
     }
-    up[r] = PARTS == 3 ? kUp : (row < BM ? ua : ub);
+    up[r] = PARTS == 3 ? kUp : pow2(row < BM ? ea : eb);
     dst[r] = 2 * row + (g ^ ((row >> 3) & 1));
   }
   // one k-tile of group r, and on to the next tile (`more`: there is one)
@@ -309,7 +311,9 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
 #pragma unroll
   for (int x = 0; x < TM; ++x) pt[x] = pdep64((uint64_t)(32 * x), maskA);
   const bool rows4 = (maskA & 3) == 3;
-  const float post = 1.f / ua / ub;
+  // the two scales taken back at once: their product reaches 2^254, whose inverse
+  // FP32 does not hold
+  auto down = [&](float v) { return PARTS == 3 ? v * (1.f / (kUp * kUp)) : __builtin_ldexpf(v, -(ea + eb)); };
   bool odd = false;
 #pragma unroll
   for (int y = 0; y < TN; ++y) {
@@ -322,8 +326,8 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const float p1 = acc[0][x][y][4 * g + q], p2 = acc[1][x][y][4 * g + q];
-          vr[q] = (p1 - p2) * post;
-          vi[q] = (acc[2][x][y][4 * g + q] - p1 - p2) * post;
+          vr[q] = down(p1 - p2);
+          vi[q] = down(acc[2][x][y][4 * g + q] - p1 - p2);
           vmax = fmaxf(vmax, fmaxf(fabsf(vr[q]), fabsf(vi[q])));
           if (PARTS == 3) odd = odd || !isfinite(vr[q]) || !isfinite(vi[q]);
         }
