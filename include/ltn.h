@@ -467,11 +467,16 @@ ltn_status ltn_execute_grad(ltn_plan* plan, const uint64_t* slice_ids, uint64_t 
 
 /* Time every distinct step shape with the candidate kernel configurations
  * on the bound stream and keep the fastest (cached in `cache_path` as JSON
- * when non-NULL). In complex64 mode on a plan bound with grad != 0, the
+ * when non-NULL; keys m<mode>_m_k_n_<bit>_bB_c2, in complex64 mode on a plan
+ * bound with grad != 0, whose forward is chosen from the FP32 tiles only,
+ * m0g_...; plans of both bindings can share a file). The suffix names the set of
+ * candidates: entries with another or none, which other versions of the library
+ * wrote, stay in the file and are not read, as are entries whose kernel does not
+ * fit its step; such steps are timed anew. In complex64 mode on a plan bound with grad != 0, the
  * adjoint products of the gradient sweep (the forward-form GEMMs of
  * ltn_execute_grad) are tuned as well: every complex64 tile (FP32 and
  * three-part) and, for sums of 2^10 and more, every split-K tile that fits each product shape in
- * either operand role, against the fixed rule (cache keys g0_m_k_n_bB,
+ * either operand role, against the fixed rule (cache keys g0_m_k_n_bB_c2,
  * values [1000 kind + cfg, swap] or [-1, 0]; a cached choice that does not
  * fit its shape falls back to the fixed rule). (Kernel choice is not part
  * of the paper's method.) Synchronises the stream. */

@@ -1702,10 +1702,42 @@ extern "C" ltn_status ltn_execute_grad(ltn_plan* p, const uint64_t* ids, uint64_
 
 namespace {
 
-std::string tune_key(int mode, const StepPlan& sp, int B) {
+// What a tuning was chosen from: a file keeps the entries of other sets, but a
+// plan does not take its kernels from them.
+constexpr char kCandidates[] = "_c2";
+
+// The complex64 forward of a plan bound for gradients has candidates of its own
+// (see bind_state), hence entries of its own.
+std::string tune_key(int mode, const StepPlan& sp, int B, bool fp32_forward) {
   std::ostringstream o;
-  o << "m" << mode << "_" << sp.m << "_" << sp.k << "_" << sp.n << "_" << (sp.c_mask_a & 1) << "_b" << B;
+  o << "m" << mode << (fp32_forward ? "g" : "") << "_" << sp.m << "_" << sp.k << "_" << sp.n << "_"
+    << (sp.c_mask_a & 1) << "_b" << B << kCandidates;
   return o.str();
+}
+
+// Why a kernel choice cannot run a step in a mode (null: it can).
+const char* misfit(const ltn_plan_impl::Choice& c, const StepPlan& sp, int mode) {
+  const int m = c.swap ? sp.n : sp.m, n = c.swap ? sp.m : sp.n;
+  const int km = c.kind == 2 ? mode : LTN_C64;
+  switch (c.kind) {
+    case 0: return c.tk == 1 || c.tk == 8 || c.tk == 64 ? nullptr : "tk must be 1, 8 or 64";
+    case 1:
+    case 2:
+      if (c.kind == 2 && mode == LTN_C64) return "split GEMM kernels need a split mode";
+      return c.cfg >= 0 && c.cfg < gemm_config_count(km) && gemm_config_fits(c.cfg, m, sp.k, n, km)
+                 ? nullptr
+                 : "tile configuration does not fit the step";
+    case 3:
+      if (c.cfg != 0 && c.cfg != 1) return "narrow kernel configuration must be 0 or 1";
+      return (c.cfg == 0 ? narrow_fits(m, sp.k, n) : narrow_rows_fits(m, sp.k, n))
+                 ? nullptr
+                 : "the narrow kernel does not fit the step";
+    case 4: return skinny_fits(sp.m, sp.k, sp.n) ? nullptr : "the split-sum kernel needs m <= 3 and n <= 3";
+    case 5:
+      return splitk_config_fits(c.cfg, m, sp.k, n) ? nullptr : "split-K tile configuration does not fit the step";
+    case 6: return parts_config_fits(c.cfg, m, sp.k, n, mode) ? nullptr : "tile configuration does not fit the step";
+  }
+  return "unknown kernel kind";
 }
 
 std::map<std::string, std::pair<int, int>> read_cache(const char* path) {
@@ -1826,7 +1858,7 @@ void tune_adjoint(ltn_plan* p, std::map<std::string, std::pair<int, int>>& cache
       const uint32_t key = adj_key(m, k, n);
       if (r.adj.count(key)) continue;
       std::ostringstream o;
-      o << "g0_" << m << "_" << k << "_" << n << "_b" << r.B;
+      o << "g0_" << m << "_" << k << "_" << n << "_b" << r.B << kCandidates;
       const auto it = cache.find(o.str());
       Choice pick;  // kind 0: the fixed rule
       if (it != cache.end()) {
@@ -1926,12 +1958,19 @@ extern "C" ltn_status ltn_autotune(ltn_plan* p, int32_t mode, const char* cache_
       if (e.first >= 0) {
         c.kind = e.first / 1000;
         c.cfg = e.first % 1000;
-        c.swap = e.second;
+        c.swap = e.second != 0;
       } else {
         c.kind = 0;
         c.tk = -e.first;
       }
       return c;
+    };
+    // a cached choice that does not fit its step is not there
+    auto cached = [&](const StepPlan& sp, Choice& c) {
+      const auto it = cache.find(tune_key(mode, sp, r.B, fp32_forward));
+      if (it == cache.end()) return false;
+      c = decode(it->second);
+      return !misfit(c, sp, mode) && !(fp32_forward && c.kind == 6);
     };
     // the synchronising time_step below must not run inside a capture
     // and a stale graph would keep the old kernels
@@ -1941,18 +1980,18 @@ extern "C" ltn_status ltn_autotune(ltn_plan* p, int32_t mode, const char* cache_
     // split-fp16 mode the per-slice maxima (not needed when every step's
     // choice comes from the cache)
     bool all_cached = true;
-    for (auto& sp : p->steps) all_cached = all_cached && cache.count(tune_key(mode, sp, r.B)) > 0;
+    Choice hit;
+    for (auto& sp : p->steps) all_cached = all_cached && cached(sp, hit);
     if (!all_cached) {
       set_ids(p, nullptr, 0, r.B, true);
       enqueue_forward(p, r.B, false, mode == LTN_C64 ? LTN_C64 : mode);
     }
     for (int s = 0; s < (int)p->steps.size(); ++s) {
       const StepPlan& sp = p->steps[s];
-      std::string key = tune_key(mode, sp, r.B);
-      auto it = cache.find(key);
+      const bool found = cached(sp, hit);
       std::vector<Choice> cands;
-      if (it != cache.end()) {
-        cands.push_back(decode(it->second));
+      if (found) {
+        cands.push_back(hit);
       } else if (sp.m + sp.k + sp.n <= kWaveWork && r.choice[mode][s].kind == 0) {
         // one launch of such a step takes its launch's 10 us on any kernel; in a
         // run it is one wave's microsecond
@@ -2044,8 +2083,8 @@ extern "C" ltn_status ltn_autotune(ltn_plan* p, int32_t mode, const char* cache_
         }
       }
       r.choice[mode][s] = pick;
-      if (it == cache.end()) {
-        cache[key] = encode(pick);
+      if (!found) {
+        cache[tune_key(mode, sp, r.B, fp32_forward)] = encode(pick);
         dirty = true;
       }
     }
@@ -2099,44 +2138,16 @@ extern "C" ltn_status ltn_set_step_kernel(ltn_plan* p, int32_t step, int32_t mod
     require(p && p->rt, "plan is not bound");
     require(step >= 0 && step < (int32_t)p->steps.size(), "step out of range");
     check_mode(mode);
-    const StepPlan& sp = p->steps[step];
-    const int m = swap ? sp.n : sp.m, n = swap ? sp.m : sp.n;
     ltn_plan_impl::Choice c;
+    c.kind = kind;
     if (kind == 0) {
-      require(tk == 1 || tk == 8 || tk == 64, "tk must be 1, 8 or 64");
       c.tk = tk;
-    } else if (kind == 1 || kind == 2) {
-      require(kind == 1 || mode != LTN_C64, "split GEMM kernels need a split mode");
-      const int km = kind == 2 ? mode : LTN_C64;
-      require(cfg >= 0 && cfg < gemm_config_count(km) && gemm_config_fits(cfg, m, sp.k, n, km),
-              "tile configuration does not fit the step");
-      c.kind = kind;
-      c.cfg = cfg;
-      c.swap = swap ? 1 : 0;
-    } else if (kind == 3) {
-      require(cfg == 0 || cfg == 1, "narrow kernel configuration must be 0 or 1");
-      require(cfg == 0 ? narrow_fits(m, sp.k, n) : narrow_rows_fits(m, sp.k, n),
-              "the narrow kernel does not fit the step");
-      c.kind = 3;
-      c.cfg = cfg;
-      c.swap = swap ? 1 : 0;
-    } else if (kind == 4) {
-      require(skinny_fits(sp.m, sp.k, sp.n), "the split-sum kernel needs m <= 3 and n <= 3");
-      c.kind = 4;
-      c.cfg = 0;
-    } else if (kind == 5) {
-      require(splitk_config_fits(cfg, m, sp.k, n), "split-K tile configuration does not fit the step");
-      c.kind = 5;
-      c.cfg = cfg;
-      c.swap = swap ? 1 : 0;
-    } else if (kind == 6) {
-      require(parts_config_fits(cfg, m, sp.k, n, mode), "tile configuration does not fit the step");
-      c.kind = 6;
-      c.cfg = cfg;
-      c.swap = swap ? 1 : 0;
     } else {
-      require(false, "unknown kernel kind");
+      c.cfg = kind == 4 ? 0 : cfg;
+      c.swap = swap && kind != 4 ? 1 : 0;
     }
+    const char* why = misfit(c, p->steps[step], mode);
+    require(!why, why ? why : "");
     drop_graphs(p);
     p->rt->choice[mode][step] = c;
   });
