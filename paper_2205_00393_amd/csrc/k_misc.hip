@@ -343,6 +343,15 @@ __global__ void k_fill_zero(uint4* p, size_t n16) {
     p[i] = make_uint4(0, 0, 0, 0);
 }
 
+// operands for timing, spread evenly over (-1, 1): the fractional parts of i times
+// the golden ratio and of i times the square root of two
+__global__ void k_fill_spread(float2* p, int64_t n) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const uint64_t x = (uint64_t)(i + 1) * 0x9e3779b97f4a7c15ull, y = (uint64_t)(i + 1) * 0x6a09e667f3bcc908ull;
+    p[i] = make_float2((float)(int32_t)(x >> 32) * 0x1p-31f, (float)(int32_t)(y >> 32) * 0x1p-31f);
+  }
+}
+
 // masked increment: the next value of pdep(z, mask) after adding pdep(d, mask)
 __device__ __forceinline__ uint64_t madd(uint64_t a, uint64_t d, uint64_t mask) {
   return ((a | ~mask) + d) & mask;
@@ -527,6 +536,10 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
   if (n16 == 0) return;
   hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(n16, 256) < 4096 ? grid_for(n16, 256) : 4096),
                      dim3(256), 0, st, (uint4*)p, n16);
+}
+
+void launch_fill_spread(float2* p, int64_t n, hipStream_t st) {
+  hipLaunchKernelGGL(k_fill_spread, dim3((unsigned)(n < (1 << 20) ? (n + 255) / 256 : 4096)), dim3(256), 0, st, p, n);
 }
 
 void launch_generic_multi(const GenericDesc* d_descs, int n, uint64_t max_outs, int nb, int tk,

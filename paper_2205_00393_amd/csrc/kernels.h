@@ -136,6 +136,8 @@ void launch_leaf_cot_accumulate(const ParamLeaf* d_pl, int n, const GatherDesc* 
 void launch_u3_adjoint(const ParamLeaf* d_pl, int n, const double* angles, const double* leafgrad,
                        double* angle_grad, hipStream_t st);
 void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
+// n numbers with parts spread over (-1, 1)
+void launch_fill_spread(float2* p, int64_t n, hipStream_t st);
 void launch_generic(const GenericDesc& d, int tk, hipStream_t st);
 // n independent descriptors (device array) in one launch over nb slices;
 // max_outs: largest 2^(xb + yb) among them

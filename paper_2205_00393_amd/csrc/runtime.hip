@@ -1492,64 +1492,52 @@ static GenericDesc adj_generic_desc(ltn_plan* p, int s, int which, int nb, int* 
   return g;
 }
 
-// Adjoint of step s (operand cotangents from the output's cotangent).
-static void enqueue_adjoint_step(ltn_plan* p, int s, int nb) {
+// The adjoint product of step s for one operand (which 0: A, 1: B), on the kernel
+// that the sweep takes for it.
+static void enqueue_adjoint_product(ltn_plan* p, int s, int which, int nb) {
   auto& r = *p->rt;
   const StepPlan& sp = p->steps[s];
-  if (!r.needs_grad[sp.out]) return;
   const TensorPlan &ta = p->tensors[sp.a], &tb = p->tensors[sp.b], &tc = p->tensors[sp.out];
-  const uint64_t cm = sp.c_mask_a;
-  {
-    // small steps and products with few columns: one kernel per operand,
-    // reading the operands in place (strided) and conjugating the second one
-    bool done[2] = {!r.needs_grad[sp.a], !r.needs_grad[sp.b]};
-    for (int which = 0; which < 2; ++which) {
-      if (done[which]) continue;
-      int tk = 1;
-      const GenericDesc g = adj_generic_desc(p, s, which, nb, &tk);
-      RowsumDesc d;
-      done[which] = true;
-      if (rowsum_fits(g, d))
-        launch_rowsum(d, r.st);
-      else if (sp.m + sp.n + sp.k <= 16)
-        launch_generic(g, tk, r.st);
-      else
-        done[which] = adj_parts_in_place(p, s, which, nb);
-    }
-    // adjoint products in the forward form: the output cotangent
-    // and the other operand are permuted so that the summed bits are
-    // lowest (and the operand conjugated), then one GEMM per operand
-    float2* Xs = reinterpret_cast<float2*>(r.ws + r.lay.gscr_c);
-    float2* Ys = reinterpret_cast<float2*>(r.ws + r.lay.gscr);
-    const int rc = sp.m + sp.n;
-    // positions of the m bits (in order) and the n bits of the output
-    std::vector<int> mpos, npos;
-    for (int j = 0; j < rc; ++j) ((cm >> j) & 1 ? mpos : npos).push_back(j);
-    if (!done[0]) {
-      // dA[m][k] = sum_n dC[merge(m, n)] conj(B[n][k])
-      std::vector<int32_t> pc(rc), pb(sp.k + sp.n);
-      for (int i = 0; i < sp.m; ++i) pc[mpos[i]] = sp.n + i;
-      for (int i = 0; i < sp.n; ++i) pc[npos[i]] = i;
-      for (int j = 0; j < sp.k; ++j) pb[j] = sp.n + j;
-      for (int i = 0; i < sp.n; ++i) pb[sp.k + i] = i;
-      const float2* X = enqueue_perm(p, arena_ptr(p, tc.gcot), Xs, pc, nb, false);
-      enqueue_perm(p, arena_ptr(p, tb.goff), Ys, pb, nb, true);
-      enqueue_nt(p, X, int64_t(1) << rc, Ys, int64_t(1) << tb.rank, arena_ptr(p, ta.gcot),
-                 int64_t(1) << ta.rank, sp.m, sp.n, sp.k, ((1ull << sp.m) - 1) << sp.k, nb);
-    }
-    if (!done[1]) {
-      // dB[n][k] = sum_m dC[merge(m, n)] conj(A[m][k])
-      std::vector<int32_t> pc(rc), pa(sp.k + sp.m);
-      for (int i = 0; i < sp.m; ++i) pc[mpos[i]] = i;
-      for (int i = 0; i < sp.n; ++i) pc[npos[i]] = sp.m + i;
-      for (int j = 0; j < sp.k; ++j) pa[j] = sp.m + j;
-      for (int i = 0; i < sp.m; ++i) pa[sp.k + i] = i;
-      const float2* X = enqueue_perm(p, arena_ptr(p, tc.gcot), Xs, pc, nb, false);
-      enqueue_perm(p, arena_ptr(p, ta.goff), Ys, pa, nb, true);
-      enqueue_nt(p, X, int64_t(1) << rc, Ys, int64_t(1) << ta.rank, arena_ptr(p, tb.gcot),
-                 int64_t(1) << tb.rank, sp.n, sp.m, sp.k, ((1ull << sp.n) - 1) << sp.k, nb);
-    }
+  const TensorPlan &self = which ? tb : ta, &other = which ? ta : tb;
+  // small steps and products with few columns: one kernel, reading the operands
+  // in place (strided) and conjugating the second one
+  int tk = 1;
+  const GenericDesc g = adj_generic_desc(p, s, which, nb, &tk);
+  RowsumDesc d;
+  if (rowsum_fits(g, d)) {
+    launch_rowsum(d, r.st);
+    return;
   }
+  if (sp.m + sp.n + sp.k <= 16) {
+    launch_generic(g, tk, r.st);
+    return;
+  }
+  if (adj_parts_in_place(p, s, which, nb)) return;
+  // forward form: the output cotangent and the other operand are permuted so that
+  // the summed bits are lowest (and the operand conjugated), then one GEMM:
+  // dA[m][k] = sum_n dC[merge(m, n)] conj(B[n][k]), dB[n][k] = sum_m dC[merge(m, n)]
+  // conj(A[m][k])
+  const int rows = which ? sp.n : sp.m, sum = which ? sp.m : sp.n, rc = sp.m + sp.n;
+  std::vector<int32_t> pc(rc), po(sp.k + sum);
+  int row = 0, at = 0;
+  for (int j = 0; j < rc; ++j) pc[j] = (int)((sp.c_mask_a >> j) & 1) != which ? sum + row++ : at++;
+  for (int j = 0; j < sp.k; ++j) po[j] = sum + j;
+  for (int i = 0; i < sum; ++i) po[sp.k + i] = i;
+  float2* Xs = reinterpret_cast<float2*>(r.ws + r.lay.gscr_c);
+  float2* Ys = reinterpret_cast<float2*>(r.ws + r.lay.gscr);
+  const float2* X = enqueue_perm(p, arena_ptr(p, tc.gcot), Xs, pc, nb, false);
+  enqueue_perm(p, arena_ptr(p, other.goff), Ys, po, nb, true);
+  enqueue_nt(p, X, int64_t(1) << rc, Ys, int64_t(1) << other.rank, arena_ptr(p, self.gcot), int64_t(1) << self.rank,
+             rows, sum, sp.k, ((1ull << rows) - 1) << sp.k, nb);
+}
+
+// Adjoint of step s (operand cotangents from the output's cotangent).
+static void enqueue_adjoint_step(ltn_plan* p, int s, int nb) {
+  const auto& need = p->rt->needs_grad;
+  const StepPlan& sp = p->steps[s];
+  if (!need[sp.out]) return;
+  for (int which = 0; which < 2; ++which)
+    if (need[which ? sp.b : sp.a]) enqueue_adjoint_product(p, s, which, nb);
 }
 
 // Adjoint sweep of one batch (steps in reverse order), then the leaf
@@ -1832,29 +1820,26 @@ float time_launch(ltn_plan* p, F&& launch, int reps, bool warm) {
   return ms / reps;
 }
 
-// Tile choice for the adjoint products of the gradient sweep (plans bound
-// for gradients, complex64): every complex64 tile that fits each product
-// shape in either operand role, against the fixed rule, timed like the
-// forward steps on the gradient scratch buffers (the values do not matter:
-// every product overwrites its output). Cache entries "g0_m_k_n_bB":
-// [1000 + cfg, swap], or [-1, 0] for the fixed rule.
+// Tile choice for the adjoint products of the gradient sweep (plans bound for
+// gradients, complex64): every complex64, split-K and three-part tile that fits a
+// product's shape in either operand role, against the fixed rule, each timed as the
+// sweep runs it (in place, or behind its permutations) on operands filled with
+// numbers of order one: what an unused arena holds may be NaN, on which the
+// three-part tiles take another way. Products that k_rowsum takes have no choice.
+// Cache entries: [1000 kind + cfg, swap], or [-1, 0] for the fixed rule.
 void tune_adjoint(ltn_plan* p, std::map<std::string, std::pair<int, int>>& cache, bool& dirty) {
   auto& r = *p->rt;
   using Choice = ltn_plan_impl::Choice;
-  float2* Xs = reinterpret_cast<float2*>(r.ws + r.lay.gscr_c);
-  float2* Ys = reinterpret_cast<float2*>(r.ws + r.lay.gscr);
-  for (const StepPlan& sp : p->steps) {
+  for (int s = 0; s < (int)p->steps.size(); ++s) {
+    const StepPlan& sp = p->steps[s];
     if (!r.needs_grad[sp.out] || sp.m + sp.n + sp.k <= 16) continue;
-    const TensorPlan &ta = p->tensors[sp.a], &tb = p->tensors[sp.b];
-    const int rc = sp.m + sp.n;
     for (int which = 0; which < 2; ++which) {
       if (!r.needs_grad[which ? sp.b : sp.a]) continue;
+      int tk;
+      RowsumDesc rd;
+      if (rowsum_fits(adj_generic_desc(p, s, which, r.B, &tk), rd)) continue;
       // dA: (m, n, k) with B's layout; dB: (n, m, k) with A's layout
       const int m = which ? sp.n : sp.m, k = which ? sp.m : sp.n, n = sp.k;
-      const TensorPlan& other = which ? ta : tb;
-      const TensorPlan& self = which ? tb : ta;
-      float2* C = arena_ptr(p, self.gcot);
-      const uint64_t cmask = ((1ull << m) - 1) << n;
       const uint32_t key = adj_key(m, k, n);
       if (r.adj.count(key)) continue;
       std::ostringstream o;
@@ -1863,7 +1848,7 @@ void tune_adjoint(ltn_plan* p, std::map<std::string, std::pair<int, int>>& cache
       Choice pick;  // kind 0: the fixed rule
       if (it != cache.end()) {
         const int kind = it->second.first >= 1000 ? it->second.first / 1000 : 0;
-        const int cfg = it->second.first % 1000, sw = it->second.second;
+        const int cfg = it->second.first % 1000, sw = it->second.second != 0;
         const int rm = sw ? n : m, rn = sw ? m : n;
         if ((kind == 1 && gemm_config_fits(cfg, rm, k, rn, LTN_C64)) ||
             (kind == 5 && splitk_config_fits(cfg, rm, k, rn)) || (kind == 6 && parts_config_fits(cfg, rm, k, rn, LTN_C64))) {
@@ -1872,15 +1857,12 @@ void tune_adjoint(ltn_plan* p, std::map<std::string, std::pair<int, int>>& cache
           pick.swap = sw;
         }
       } else {
+        const TensorPlan &tc = p->tensors[sp.out], &other = p->tensors[which ? sp.a : sp.b];
+        launch_fill_spread(arena_ptr(p, tc.gcot), ((int64_t)r.B << tc.rank), r.st);
+        launch_fill_spread(arena_ptr(p, other.goff), ((int64_t)r.B << other.rank), r.st);
         auto run = [&](const Choice& c) {
-          if (c.kind > 0) {
-            nt_gemm(p, Xs, int64_t(1) << rc, Ys, int64_t(1) << other.rank, C, int64_t(1) << self.rank,
-                    m, k, n, cmask, r.B, c.kind, c.swap, c.cfg);
-          } else {
-            r.adj.erase(key);
-            enqueue_nt(p, Xs, int64_t(1) << rc, Ys, int64_t(1) << other.rank, C, int64_t(1) << self.rank,
-                       m, k, n, cmask, r.B);
-          }
+          r.adj[key] = c;
+          enqueue_adjoint_product(p, s, which, r.B);
         };
         std::vector<Choice> cands(1);
         for (int sw = 0; sw < 2; ++sw)
