@@ -109,9 +109,9 @@ __device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)
 // conjugated (adjoint products on the operands of the forward step). The lanes of
 // an operand run along its sum as above where that has the lowest address bit,
 // else along its rows, whose elements are then neighbours.
-// 256 slices, permutations of both operands and the plain tile -> in place: (11 rows,
-// sum 9, 7 columns) 1.93 -> 1.29 ms, (9,11,7) 2.05 -> 1.47, (10,6,10) 0.91 -> 1.10 and
-// (6,10,10) 1.56 -> 0.82.
+// 256 slices, permutations and the plain tile -> in place: (11 rows, sum 9, 7 columns)
+// 1.93 -> 1.29 ms, (9,11,7) 2.05 -> 1.47, (6,10,10) 1.61 -> 0.92, but (10,6,10) 1.05 ->
+// 1.16: the caller takes it by what there is to permute.
 template <int BM, int BN, int PARTS, bool SPLITK, bool INPLACE>
 __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   constexpr int T = 256, KT = 16, NWM = 2, NWN = 2;

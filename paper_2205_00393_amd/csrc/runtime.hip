@@ -1386,10 +1386,21 @@ static void enqueue_nt(ltn_plan* p, const float2* X, int64_t sX, const float2* Y
   launch_generic(g, default_tk(k, (1ull << (m + n)) * (uint64_t)nb), r.st);
 }
 
+// Whether a parts tile reads the operands of an adjoint product where they lie: the
+// product itself then takes 12-30 % longer, so it pays where there is enough to
+// permute. The cotangent has 2^-cols of the product's multiply-adds in elements (none
+// to move if its rows are the upper bits already), the other operand 2^-rows; in
+// place from 2^-8 on. 256 slices, permuted against in place, us: (rows 10, cols 10,
+// sum 7) 1558 and 1728, (11,9,6) 522 and 550, (9,7,7) in order 119 and 129, (10,6,10)
+// in order 820 and 1077; (8,7,8) in order 113 and 106, (11,7,5) 238 and 218, (9,7,7)
+// 162 and 125, (10,6,10) 1604 and 1020.
+static bool in_place_pays(int rows, int cols, bool in_order) {
+  return rows <= 8 || (!in_order && (cols <= 8 || (rows == 9 && cols == 9)));
+}
+
 // The adjoint product of step s for one operand (which 0: A, 1: B) on a parts
 // tile that reads the output's cotangent and the other operand where they lie;
-// false where the product takes another kernel. What the permutations took goes
-// (20-qubit gradient: 2.5 of 12.2 ms), the product itself takes 3-30 % longer.
+// false where the product takes another kernel.
 static bool adj_parts_in_place(ltn_plan* p, int s, int which, int nb) {
   auto& r = *p->rt;
   const StepPlan& sp = p->steps[s];
@@ -1410,9 +1421,9 @@ static bool adj_parts_in_place(ltn_plan* p, int s, int which, int nb) {
       cfg = parts_config_default(n, k, m, nb, LTN_C64);
     }
   }
-  if (cfg < 0 || !parts_config_in_place(cfg)) return false;
   const uint64_t cfull = (1ull << (sp.m + sp.n)) - 1, ofull = (1ull << (m + n)) - 1;
   const uint64_t xrow = which ? ~sp.c_mask_a & cfull : sp.c_mask_a, yrow = (1ull << n) - 1;
+  if (cfg < 0 || !parts_config_in_place(cfg) || !in_place_pays(m, n, (cfull & ~xrow) == (1ull << k) - 1)) return false;
   const uint64_t ysum = ((1ull << k) - 1) << n, cmask = ((1ull << m) - 1) << n;
   const float2 *X = arena_ptr(p, tc.gcot), *Y = arena_ptr(p, other.goff);
   GemmDesc d{};
