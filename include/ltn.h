@@ -515,7 +515,10 @@ ltn_status ltn_permute(const void* d_in, void* d_out, int32_t rank, const int32_
  * matrix cores, tiles down to 16 complex columns, FP32 partials added in
  * chunk order by a second pass), 6 = complex64 GEMM on bf16 MFMA: each real
  * operand as three bf16 parts whose sum is the FP32 value, the six largest
- * products of parts summed in FP32 (cfg 0, 1: full tiles; 2, 3: split-K), or
+ * products of parts summed in FP32 (cfg 0, 1: full tiles; 2, 3: split-K; output
+ * tiles with an infinity, NaN, an operand above 2^104 or a result above 2^79 are
+ * computed once more on the FP32 matrix cores: the values are those of kind 1, a
+ * step in which every tile is such a one takes 2.6 times as long), or
  * in split fp16 mode as two scaled fp16 parts on sums of 2^10 and more (cfg 4:
  * full, 5: split-K);
  * cfg = tile configuration of that

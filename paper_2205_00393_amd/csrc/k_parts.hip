@@ -53,9 +53,10 @@ typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 
 // The last part of a number below 2^-110 falls below bf16's smallest number.
 // Circuits have such entries (cos(pi/2) = 6e-17 and its products), so operands
-// are scaled up by 2^24, which makes every FP32 number above 2^-126 exact; what
-// overflows then (results above 2^79) takes the FP32 way at the end. 48
-// multiplications per wave and k-tile: 1-2 % of the time.
+// are scaled up by 2^24, which makes every FP32 number above 2^-126 exact; tiles in
+// which something overflows then (operands above 2^104, results above 2^79) are
+// computed again at the end, on the FP32 matrix cores. 48 multiplications per wave
+// and k-tile: 1-2 % of the time.
 constexpr float kUp = 0x1p24f;
 
 // Parts of eight FP32 values times `up`, as the operand words of one MFMA lane.
@@ -234,14 +235,17 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   };
 
   floatx16 acc[3][TM][TN];
+  auto clear = [&]() {
 #pragma unroll
-  for (int p = 0; p < 3; ++p)
+    for (int p = 0; p < 3; ++p)
 #pragma unroll
-    for (int x = 0; x < TM; ++x)
+      for (int x = 0; x < TM; ++x)
 #pragma unroll
-      for (int y = 0; y < TN; ++y)
+        for (int y = 0; y < TN; ++y)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[p][x][y][v] = 0.f;
+          for (int v = 0; v < 16; ++v) acc[p][x][y][v] = 0.f;
+  };
+  clear();
 
   auto unit = [&](int row) { return 2 * row + (h ^ ((row >> 3) & 1)); };
   auto multiply = [&](int pl) {
@@ -286,6 +290,73 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
     multiply(2);
   }
 
+  // Re and Im from the three products, in the place of the first and the third;
+  // whether any of them is not finite
+  auto combine = [&]() {
+    float none = 0.f;
+#pragma unroll
+    for (int x = 0; x < TM; ++x)
+#pragma unroll
+      for (int y = 0; y < TN; ++y)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float p1 = acc[0][x][y][v], p2 = acc[1][x][y][v];
+          acc[0][x][y][v] = p1 - p2;
+          acc[2][x][y][v] = acc[2][x][y][v] - p1 - p2;
+          if (PARTS == 3) none = fmaf(acc[0][x][y][v], 0.f, fmaf(acc[2][x][y][v], 0.f, none));
+        }
+    return none != none;
+  };
+  bool odd = combine();
+  float post = 1.f / (kUp * kUp);
+  if constexpr (PARTS == 3) {
+    // Infinities, NaN, or a number too large for the scaled parts: the block's tile
+    // again on the FP32 matrix cores, three products as before. A thread takes a row
+    // of a k-tile (stride 17 in LDS: no bank conflicts). Bound by those cores:
+    // (13,12,11) with NaN everywhere 5.4 ms, of which 3.3 here, as on the FP32 tiles
+    // (3.1); with each lane summing its own outputs 146 ms.
+    if (__syncthreads_or(odd)) {
+      constexpr int LD = KT + 1, PL = ROWS * LD;
+      static_assert(ROWS <= T && 3 * PL * sizeof(float) <= sizeof(S), "a thread per row, three planes");
+      float* F = reinterpret_cast<float*>(S);
+      const int me = 64 * wave + __lane_id(), col = me - BM;
+      const float2* row = me < BM ? A + (INPLACE ? (int64_t)pdep64((uint64_t)me, d.arow) : me * K)
+                                   : B + (INPLACE ? (int64_t)pdep64((uint64_t)(col & (BN - 1)), d.brow) : col * K);
+      const uint64_t sum = me < BM ? d.asum : d.bsum;
+      const float sign = INPLACE && (me < BM ? d.conj_a : d.conj_b) ? -1.f : 1.f;
+      uint64_t z = 0;
+      clear();
+      for (int t = 0; t < nt; ++t) {
+        __syncthreads();
+        if (me < ROWS) {
+#pragma unroll 8
+          for (int q = 0; q < KT; ++q) {
+            const float2 v = row[z];
+            z = INPLACE ? ((z | ~sum) + 1) & sum : z + 1;
+            float* f = F + me * LD + q;
+            f[0] = v.x;
+            f[PL] = v.y * sign;
+            f[2 * PL] = v.x + v.y * sign;
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl)
+#pragma unroll 2
+          for (int q = 0; q < KT; q += 2)
+#pragma unroll
+            for (int x = 0; x < TM; ++x)
+#pragma unroll
+              for (int y = 0; y < TN; ++y)
+                acc[pl][x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                    F[pl * PL + (wm * WM + 32 * x + i) * LD + q + h],
+                    F[pl * PL + (BM + wn * WN + 32 * y + i) * LD + q + h], acc[pl][x][y], 0, 0, 0);
+      }
+      combine();
+      post = 1.f;
+    }
+  }
+
   const uint64_t maskA = SPLITK ? ((uint64_t)(M - 1) << d.n) : d.cmask;
   const uint64_t maskB = ~maskA & ((1ull << (d.m + d.n)) - 1);
   const float so =
@@ -313,8 +384,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
   const bool rows4 = (maskA & 3) == 3;
   // the two scales taken back at once: their product reaches 2^254, whose inverse
   // FP32 does not hold
-  auto down = [&](float v) { return PARTS == 3 ? v * (1.f / (kUp * kUp)) : __builtin_ldexpf(v, -(ea + eb)); };
-  bool odd = false;
+  auto down = [&](float v) { return PARTS == 3 ? v * post : __builtin_ldexpf(v, -(ea + eb)); };
 #pragma unroll
   for (int y = 0; y < TN; ++y) {
     const uint64_t pn = pdep64((uint64_t)(col0 + 32 * y + i), maskB);
@@ -325,11 +395,9 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
         float vr[4], vi[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const float p1 = acc[0][x][y][4 * g + q], p2 = acc[1][x][y][4 * g + q];
-          vr[q] = down(p1 - p2);
-          vi[q] = down(acc[2][x][y][4 * g + q] - p1 - p2);
+          vr[q] = down(acc[0][x][y][4 * g + q]);
+          vi[q] = down(acc[2][x][y][4 * g + q]);
           vmax = fmaxf(vmax, fmaxf(fabsf(vr[q]), fabsf(vi[q])));
-          if (PARTS == 3) odd = odd || !isfinite(vr[q]) || !isfinite(vi[q]);
         }
         const uint64_t a0 = pbase | pt[x] | pg[g] | pn;
         if (rows4) {
@@ -352,30 +420,6 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_parts(GemmDesc d) {
           for (int q = 0; q < 4; ++q) put(a0 | pq[q], vr[q], vi[q]);
         }
       }
-  }
-  if (PARTS == 3 && odd) {
-    // infinities, NaN, or a number too large for the scaled parts: this lane's
-    // outputs again, in FP32 from the operands
-    vmax = 0.f;
-    for (int e = 0; e < 16 * TM * TN; ++e) {
-      const int64_t row = wm * WM + 32 * (e / (16 * TN)) + 8 * ((e >> 2) & 3) + 4 * h + (e & 3);
-      const int64_t col = wn * WN + 32 * ((e >> 4) % TN) + i;
-      const float2* a = A + (INPLACE ? (int64_t)pdep64((uint64_t)row, d.arow) : row * K);
-      const float2* q = B + (INPLACE ? (int64_t)pdep64((uint64_t)col, d.brow) : col * K);
-      float p1 = 0.f, p2 = 0.f, p3 = 0.f;
-      for (int64_t k = 0; k < KL; ++k) {
-        float2 u = a[INPLACE ? (int64_t)pdep64((uint64_t)k, d.asum) : k];
-        float2 v = q[INPLACE ? (int64_t)pdep64((uint64_t)k, d.bsum) : k];
-        if (INPLACE && d.conj_a) u.y = -u.y;
-        if (INPLACE && d.conj_b) v.y = -v.y;
-        p1 = fmaf(u.x, v.x, p1);
-        p2 = fmaf(u.y, v.y, p2);
-        p3 = fmaf(u.x + u.y, v.x + v.y, p3);
-      }
-      const float re = p1 - p2, im = p3 - p1 - p2;
-      vmax = fmaxf(vmax, fmaxf(fabsf(re), fabsf(im)));
-      put(pdep64((uint64_t)(bm * BM + row), maskA) | pdep64((uint64_t)(bn * BN + col), maskB), re, im);
-    }
   }
   if (!SPLITK && d.scale_c) block_raise_max(d.scale_c + b, vmax, reinterpret_cast<float*>(S));
 }
