@@ -1249,14 +1249,20 @@ extern "C" ltn_status ltn_execute_scratch(ltn_plan* p, const uint64_t* ids, uint
       bind_state(p, &tmp, ws, LTN_SCRATCH_BYTES, 0, reinterpret_cast<hipStream_t>(stream), B, mode);
       build_fwd_seq(p, mode, false);
       // leaf data and descriptors, which lie in a row, in one copy (three with
-      // two waits took 20 of a 12-qubit amplitude's 64 us)
+      // two waits took 20 of a 12-qubit amplitude's 64 us); leaf data above 1 MiB
+      // from where they are, as gathering them on the host costs more (512 KiB: 72
+      // against 84 us a call, 2 MiB: 180 against 134, 8 MiB: 530 against 306)
       const auto& descs = tmp.fseq_descs[mode];
       const size_t fdesc = tmp.lay.fdesc + (size_t)mode * p->steps.size() * sizeof(GenericDesc);
-      std::vector<char> host(fdesc + descs.size() * sizeof(GenericDesc));
-      std::memcpy(host.data() + tmp.lay.leafdata, p->leaf_data.data(), (size_t)p->leaf_elems * 8);
-      std::memcpy(host.data() + tmp.lay.gd_fwd, tmp.gd_fwd.data(), tmp.gd_fwd.size() * sizeof(GatherDesc));
-      std::memcpy(host.data() + fdesc, descs.data(), descs.size() * sizeof(GenericDesc));
-      HIPCHECK(hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice, tmp.st));
+      const size_t leaf_bytes = (size_t)p->leaf_elems * 8, from = leaf_bytes > (1 << 20) ? tmp.lay.gd_fwd : 0;
+      std::vector<char> host(fdesc - from + descs.size() * sizeof(GenericDesc));
+      if (from)
+        HIPCHECK(hipMemcpyAsync(ws + tmp.lay.leafdata, p->leaf_data.data(), leaf_bytes, hipMemcpyHostToDevice, tmp.st));
+      else
+        std::memcpy(host.data() + tmp.lay.leafdata, p->leaf_data.data(), leaf_bytes);
+      std::memcpy(host.data() + (tmp.lay.gd_fwd - from), tmp.gd_fwd.data(), tmp.gd_fwd.size() * sizeof(GatherDesc));
+      std::memcpy(host.data() + (fdesc - from), descs.data(), descs.size() * sizeof(GenericDesc));
+      HIPCHECK(hipMemcpyAsync(ws + from, host.data(), host.size(), hipMemcpyHostToDevice, tmp.st));
       HIPCHECK(hipStreamSynchronize(tmp.st));
       for (uint64_t off = 0; off < n; off += (uint64_t)B) {
         const int nb = (int)std::min<uint64_t>((uint64_t)B, n - off);
