@@ -470,7 +470,9 @@ const char* parts_config_name(int cfg, int mode) {
 // 128 x 64 tiles ((13,10,10), 512 tiles: 0.286 ms; (18,6,6): 0.081 against
 // 0.085 on the best FP32 tile); with one per CU, the split-K form on sums from
 // 2^11 ((13,11,9): 0.302 against 0.347, (11,12,11): 0.55 against 0.69) and
-// full tiles on shorter ones ((11,10,11): 0.163 against 0.177, FP32 0.221).
+// full tiles on shorter ones ((11,10,11): 0.163 against 0.177, FP32 0.221) down to
+// 2^6 ((12,6,10): 25.7 us, FP32 27.5; (14,5,8) 21.0 and 20.2). Sums of 2^4 take 64
+// columns on FP32 ((18,4,6): 65 us on parts, 45 on FP32; (18,5,6) 58 on both).
 // Fewer tiles: split-K where its chunks give half a block per CU ((10,10,10):
 // 0.065 against 0.076 ms on the best FP32 tile, (13,14,7): 0.55 against 0.90;
 // (7,12,7), 16 blocks: 0.053 against 0.029; full tiles, (11,10,10): 0.136
@@ -501,7 +503,8 @@ int parts_config_default(int m, int k, int n, int64_t nb, int mode) {
     split = wide ? 2 : 3;
   }
   if (full >= 0 && parts_config_fits(full, m, k, n, mode) &&
-      (tiles >= 512 || (wide && tiles >= 256 && (k < (f16 ? 12 : 11) || !parts_config_fits(split, m, k, n, mode)))))
+      (tiles >= 512 ? wide || k >= 5
+                    : wide && tiles >= 256 && k >= 6 && (k < (f16 ? 12 : 11) || !parts_config_fits(split, m, k, n, mode))))
     return full;
   if (!parts_config_fits(split, m, k, n, mode) || (tiles << splitk_chunk_bits(m, k, n)) < 128) return -1;
   return tiles < 512 ? split : -1;

@@ -190,14 +190,22 @@ int default_cfg(int m, int k, int n) {
 // of 128 x 64: 0.074 against 0.114; (10,10,10), 64 x 64: 0.056 against 0.107).
 // Shorter sums with many tiles write more than they multiply: the register-
 // staged 128 x 64 tile ((14,4,12): 0.113 against 0.118 for 128 x 128 and
-// 0.129 with DMA).
+// 0.129 with DMA). fp16 tiles raise a slice's maximum once a wave, and the waves of
+// several slices queue at neighbouring slots: there the largest register-staged
+// tiles ((10,4,8) x 32: 0.044 against 0.076 ms for 128 x 64, (9,4,8) x 256 0.095 against
+// 0.120, (9,4,7) x 16 0.023 against 0.031 for 64 x 64; at 2^18 outputs 64 x 64 is 5 %
+// faster), and for one slice from 2^22 outputs, where they are even. Sums of 2^6 are
+// touched at 2^20 outputs only ((8,6,7) x 32: 0.027 against 0.032; 0.90 and 1.00 of the
+// time a factor of two below and above).
 int default_split_cfg(int m, int k, int n, int64_t nb, int mode) {
   const int64_t outs = m + n > 40 ? int64_t(1) << 40 : (int64_t(1) << (m + n)) * nb;
   const bool many = outs >> 14 >= 256, half = outs >> 13 >= 256;
+  const bool queued = mode == LTN_SPLIT_F16 && (k < 6 ? (nb > 1 ? outs >> 19 : outs >> 22) > 0
+                                                      : k == 6 && nb > 1 && !half && outs >> 20 > 0);
   static const int large[] = {10, 11, 12, 13}, middle[] = {11, 12, 13}, small_[] = {13}, brief[] = {1, 2, 3};
   const int* order = k >= 6 ? (many ? large : half ? middle : small_) : (many ? brief : small_);
   const int len = k >= 6 ? (many ? 4 : half ? 3 : 1) : (many ? 3 : 1);
-  for (int i = 0; i < len; ++i)
+  for (int i = 0; i < len && !queued; ++i)
     if (gemm_config_fits(order[i], m, k, n, mode)) return order[i];
   for (int c = 0; c < gemm_config_count(mode); ++c)
     if (gemm_config_fits(c, m, k, n, mode)) return c;
@@ -1068,10 +1076,15 @@ void bind_state(ltn_plan* p, ltn_plan_impl* r, char* d_ws, size_t bytes, int gra
       // short sums of 2 and 4 with many outputs: the direct tiles 64 x 32 x 2
       // and x 4 (64 slices of (7,2,7): 0.009 ms against 0.019 on the generic
       // kernel, (8,1,6): 0.009 against 0.011 on the narrow one, (13,1,10): 0.029
-      // against 0.151; at 2^17 outputs, (6,2,6) x 32, no gain)
-      if (ch.kind == 0 && (mode != LTN_C64 || !grad) && (sp.k == 1 || sp.k == 2) && sp.m + sp.n < 40 &&
-          (int64_t(1) << (sp.m + sp.n)) * B >= int64_t(1) << 18) {
-        const bool nat = (sp.c_mask_a & 1) != 0;
+      // against 0.151; at 2^17 outputs, (6,2,6) x 32, no gain). Not from 2^21 outputs
+      // on where the narrow kernel fits, the rows hold the output's lowest bit and no
+      // maxima are recorded: (16,1,6) 16.6 us narrow and 18.4 here, (11,1,6) x 256 76 and
+      // 89, (17,2,6) x 4 85 and 98; lowest bit from the columns, (12,2,5) x 256, 111 and 93.
+      const bool nat = (sp.c_mask_a & 1) != 0, tall = sp.m >= sp.n;
+      const int64_t outs = sp.m + sp.n < 40 ? (int64_t(1) << (sp.m + sp.n)) * B : 0;
+      const bool narrow = mode != LTN_SPLIT_F16 && nat == tall && outs >> 21 > 0 &&
+                          narrow_fits(tall ? sp.m : sp.n, sp.k, tall ? sp.n : sp.m);
+      if (ch.kind == 0 && (mode != LTN_C64 || !grad) && (sp.k == 1 || sp.k == 2) && outs >> 18 > 0 && !narrow) {
         const int c = sp.k == 1 ? 7 : 6;
         for (bool sw : {nat, !nat})
           if (ch.kind == 0 && gemm_config_fits(c, sw ? sp.n : sp.m, sp.k, sw ? sp.m : sp.n, LTN_C64)) {
