@@ -252,14 +252,17 @@ __global__ __launch_bounds__(256) void k_narrow_rows(NarrowDesc d) {
 // 0.046 ms, with U = 1 0.075 (blocks of 2 KiB are gone before their loads are
 // back); (23,1,1) 0.046 and 0.063, (22,2,2) 0.048 and 0.056. From K N = 32 on a row
 // has the loads already, and two rows' products crowd the registers ((21,3,3): 0.123
-// against 0.058). Fewer than 256 such blocks leave CUs idle.
+// against 0.058). Fewer than 256 such blocks leave CUs idle; from U = 8 on, 128 are
+// still better than 128 U of one row a thread ((19,0,0): 8.2 against 14.5 us, the tiles
+// 11.3), and 64 where each block raises a slice's maximum, for which it queues
+// ((16,0,0) x 4: 8.9 against 15.6 us, tiles 11.8; (13,1,1) x 32: 9.4 against 14.8).
 template <int K, int N>
 void launch_rows_kn(const NarrowDesc& d, hipStream_t st) {
   constexpr int U = K * N <= 16 ? 16 / (K > N ? K : N) : 1;
   const int64_t rows = (int64_t(1) << d.m) * d.nb;
   const auto grid = [&](int u) { return dim3((unsigned)std::min<int64_t>(rows / (256 * u), 8192)); };
   if constexpr (U > 1)
-    if ((int64_t(1) << d.m) >= 256 * U && rows >= 256 * 256 * U) {
+    if ((int64_t(1) << d.m) >= 256 * U && rows >= int64_t(256) * U * (U < 8 ? 256 : d.scale_c ? 64 : 128)) {
       hipLaunchKernelGGL((k_narrow_rows<K, N, U>), grid(U), dim3(256), 0, st, d);
       return;
     }

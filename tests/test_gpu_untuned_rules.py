@@ -12,12 +12,14 @@ pytestmark = pytest.mark.gpu
 
 # (m, k, n), slices, mode, the other kernel's kind and tile: split fp16 tiles of
 # several slices, sums of 2^4 and 2^6, and of one slice; 64 columns and one tile a CU on
-# three parts; narrow steps whose rows hold the output's lowest bit
+# three parts; narrow steps whose rows hold the output's lowest bit; rows of one element
+# with and without maxima
 @pytest.mark.parametrize("m,k,n,sl,mode,kind,cfg", [
     (10, 4, 8, 5, "split_f16", 2, 0), (11, 4, 7, 4, "split_f16", 2, 0), (9, 4, 8, 8, "split_f16", 2, 0),
     (8, 6, 7, 5, "split_f16", 2, 0), (15, 5, 8, 0, "split_f16", 2, 0), (18, 4, 6, 0, "c64", 1, 13),
     (15, 4, 7, 0, "c64", 1, 10), (17, 1, 6, 2, "c64", 3, 0), (11, 1, 6, 8, "split_bf16", 3, 0),
-    (17, 2, 6, 2, "c64", 3, 0)])
+    (17, 2, 6, 2, "c64", 3, 0), (19, 0, 0, 0, "c64", 3, 0), (16, 0, 0, 2, "split_f16", 3, 0),
+    (13, 1, 1, 5, "split_f16", 3, 0)])
 def test_untuned_choice_is_not_slow(torch, m, k, n, sl, mode, kind, cfg):  # noqa: F811
     import paper_2205_00393_amd as P
     rng = np.random.default_rng(m + k + n)
