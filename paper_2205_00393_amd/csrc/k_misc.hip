@@ -424,9 +424,10 @@ __device__ __forceinline__ void generic_body(const GenericDesc& d, uint64_t blk,
   if (d.scale_out) {
     // every thread is here again: one atomic if all of the block that hold a
     // value share its first slice, else one per wave whose lanes share one,
-    // else one per lane
+    // else one per lane. Blocks that go round the outputs again have several
+    // slices behind them: their waves don't wait for each other.
     const uint64_t first = (blk * per_block) >> (d.xb() + d.yb());
-    if (__syncthreads_and(bcur == first || bcur == ~0ull)) {
+    if (total <= nblk * per_block && __syncthreads_and(bcur == first || bcur == ~0ull)) {
       block_raise_max(d.scale_out + first, vcur);
     } else {
       const uint64_t b0 = __shfl(bcur, 0, 64);
