@@ -466,6 +466,8 @@ const char* parts_config_name(int cfg, int mode) {
   return cfg >= 0 && cfg < parts_config_count(mode) ? kParts[cfg].name : "?";
 }
 
+bool parts_config_in_place(int cfg) { return cfg == 0 || cfg == 1; }
+
 // complex64: full tiles where two 128 x 128 tiles per CU can share it, or two
 // 128 x 64 tiles ((13,10,10), 512 tiles: 0.286 ms; (18,6,6): 0.081 against
 // 0.085 on the best FP32 tile); with one per CU, the split-K form on sums from
@@ -486,9 +488,9 @@ const char* parts_config_name(int cfg, int mode) {
 // where a long sum leaves at most one 64 x 64 split tile per CU ((13,14,7) 0.59
 // against 1.16 ms, (14,13,6) 0.40 against 0.81; with two per CU, (12,13,9):
 // 0.59 against 0.51, and with a shorter sum, (10,12,10): 0.171 against 0.148).
-bool parts_config_in_place(int cfg) { return cfg == 0 || cfg == 1; }
-
-int parts_config_default(int m, int k, int n, int64_t nb, int mode) {
+// In place the short sums stay on parts, as FP32 tiles want permuted operands
+// (11 rows, sum of 2^4, 7 columns x 256: 176 us, permuted 185).
+int parts_config_default(int m, int k, int n, int64_t nb, int mode, bool in_place) {
   if (m < 7 || n < 6 || m + n > 40) return -1;
   const bool wide = n >= 7, f16 = mode == LTN_SPLIT_F16;
   const int64_t outs = (int64_t(1) << (m + n)) * nb, tiles = outs >> (wide ? 14 : 13);
@@ -503,8 +505,9 @@ int parts_config_default(int m, int k, int n, int64_t nb, int mode) {
     split = wide ? 2 : 3;
   }
   if (full >= 0 && parts_config_fits(full, m, k, n, mode) &&
-      (tiles >= 512 ? wide || k >= 5
-                    : wide && tiles >= 256 && k >= 6 && (k < (f16 ? 12 : 11) || !parts_config_fits(split, m, k, n, mode))))
+      (tiles >= 512 ? wide || k >= 5 || in_place
+                    : wide && tiles >= 256 && (k >= 6 || in_place) &&
+                          (k < (f16 ? 12 : 11) || !parts_config_fits(split, m, k, n, mode))))
     return full;
   if (!parts_config_fits(split, m, k, n, mode) || (tiles << splitk_chunk_bits(m, k, n)) < 128) return -1;
   return tiles < 512 ? split : -1;

@@ -17,9 +17,9 @@
 //
 // What bounds it: latency (a barrier, descriptor and LDS round trip per level).
 // Measured per call, launches of independent steps -> runs: 12-qubit circuit
-// (24 steps, one slice) 66 -> 26 us, in the library's scratch 137 -> 64 us;
-// 20-qubit circuit, 256 slices, complex64 167 -> 77 us (88 with one group), split
-// fp16 594 us (669 with one group).
+// (24 steps, one slice) 66 -> 26 us; 20-qubit circuit of 16 slices, complex64, 167 ->
+// 77 us (88 with one group); of 256 slices in batches of 96, split fp16, 594 us (669
+// with one group).
 #include <cstddef>
 
 #include "kernels.h"

@@ -284,15 +284,15 @@ void launch_cgemm_splitk(const GemmDesc& d, hipStream_t st);
 // Second pass of a split-K product: the chunks' partials added into C.
 void launch_splitk_reduce(const GemmDesc& d, hipStream_t st);
 // The complex64 product from three bf16 parts of each real operand, formed
-// while the tiles are staged (k_parts.hip); full and split-K tiles.
-// in split fp16 mode also tiles on two scaled fp16 parts (scale_a, scale_b).
+// while the tiles are staged (k_parts.hip); full and split-K tiles; in split
+// fp16 mode also tiles on two scaled fp16 parts (scale_a, scale_b).
 int parts_config_count(int mode);
 bool parts_config_fits(int cfg, int m, int k, int n, int mode);
 bool parts_config_splitk(int cfg);
 const char* parts_config_name(int cfg, int mode);
-// Untuned rule: the configuration to take for nb slices, or -1.
 bool parts_config_in_place(int cfg);  // takes arow .. conj_b
-int parts_config_default(int m, int k, int n, int64_t nb, int mode);
+// Untuned rule: the configuration to take for nb slices, or -1.
+int parts_config_default(int m, int k, int n, int64_t nb, int mode, bool in_place = false);
 void launch_cgemm_parts(const GemmDesc& d, hipStream_t st);
 // complex64 tensor X (2^rank per slice, rank >= 2) -> its split-layout
 // copy Y in the given split mode (fp16 scaled by the per-slice max slot[b]).

@@ -1434,10 +1434,10 @@ static bool adj_parts_in_place(ltn_plan* p, int s, int which, int nb) {
     sw = tuned->second.swap;
     cfg = tuned->second.cfg;
   } else {
-    cfg = parts_config_default(m, k, n, nb, LTN_C64);
+    cfg = parts_config_default(m, k, n, nb, LTN_C64, true);
     if (cfg < 0) {
       sw = true;
-      cfg = parts_config_default(n, k, m, nb, LTN_C64);
+      cfg = parts_config_default(n, k, m, nb, LTN_C64, true);
     }
   }
   const uint64_t cfull = (1ull << (sp.m + sp.n)) - 1, ofull = (1ull << (m + n)) - 1;
