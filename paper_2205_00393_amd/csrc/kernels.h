@@ -291,6 +291,7 @@ bool parts_config_fits(int cfg, int m, int k, int n, int mode);
 bool parts_config_splitk(int cfg);
 const char* parts_config_name(int cfg, int mode);
 bool parts_config_in_place(int cfg);  // takes arow .. conj_b
+bool parts_config_yields(int cfg, int m, int k, int n, int mode);  // to its split-K form
 // Untuned rule: the configuration to take for nb slices, or -1.
 int parts_config_default(int m, int k, int n, int64_t nb, int mode, bool in_place = false);
 void launch_cgemm_parts(const GemmDesc& d, hipStream_t st);

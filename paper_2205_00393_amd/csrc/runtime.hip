@@ -2055,7 +2055,8 @@ extern "C" ltn_status ltn_autotune(ltn_plan* p, int32_t mode, const char* cache_
             }
         for (int sw = 0; sw < 2 && !fp32_forward; ++sw)
           for (int c = 0; c < parts_config_count(mode); ++c)
-            if (sw ? parts_config_fits(c, sp.n, sp.k, sp.m, mode) : parts_config_fits(c, sp.m, sp.k, sp.n, mode)) {
+            if ((sw ? parts_config_fits(c, sp.n, sp.k, sp.m, mode) : parts_config_fits(c, sp.m, sp.k, sp.n, mode)) &&
+                !parts_config_yields(c, sw ? sp.n : sp.m, sp.k, sw ? sp.m : sp.n, mode)) {
               Choice ch;
               ch.kind = 6;
               ch.cfg = c;
