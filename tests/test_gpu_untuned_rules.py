@@ -49,6 +49,8 @@ def test_untuned_choice_is_not_slow(torch, m, k, n, sl, mode, kind, cfg):  # noq
         us = best()
         if other is None or us < other:
             other, want = us, plan.execute_range(0, 1 << sl, mode=mode)
+    plan.set_step_kernel(0, mode, *own)
+    mine = min(mine, best())  # before and after: the first launches may run at low clocks
     banner(f"({step['m']},{k},{step['n']}) x {1 << sl} {mode}: {name} (swap {own[2]}) {mine:.1f} us, "
            f"{P.kernel_name(kind, cfg, mode)} {other:.1f} us")
     assert rel_l2(got.cpu().numpy(), want.cpu().numpy()) < 1e-5
